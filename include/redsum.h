@@ -326,9 +326,19 @@ int red_sum_segmented_loop(const float *x, const int64_t *host_offsets, int64_t 
  *                                    (device-scope atomic stores and loads)
  *                                    at a grid barrier every steps_per_sync
  *                                    steps;
- *            RED_VARIANT_AUTO        persistent when the array's windows fit
- *                                    the co-resident workgroups, else
- *                                    relaunch.
+ *            RED_VARIANT_AUTO        many steps per launch: each wavefront
+ *                                    advances a window of the array in its
+ *                                    registers, with margins that
+ *                                    neighbouring windows recompute, u and
+ *                                    scratch alternating over an even
+ *                                    number of ordinary launches (one, in
+ *                                    place, up to 514 values); any length.
+ *                                    steps_per_sync and the launch flags
+ *                                    below concern the persistent form and
+ *                                    are not used here.  With plan.wg or
+ *                                    plan.grid set: persistent when the
+ *                                    array's windows fit the co-resident
+ *                                    workgroups, else relaunch.
  *            plan.wg (persistent default: the fewest values per thread, 2
  *            to 32, whose workgroup stays within 1024 threads and is
  *            co-resident with the grid; relaunch default 512; a caller's

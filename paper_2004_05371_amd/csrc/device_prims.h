@@ -103,6 +103,13 @@ __device__ __forceinline__ T dpp_move(T v) {
   return r;
 }
 
+// DPP move of one word in which lanes whose source is invalid keep `old`.
+template <int CTRL>
+__device__ __forceinline__ float dpp_update(float old, float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
 template <class T>
 __device__ __forceinline__ T read_lane(T v, int lane) {
   int w[Words<T>::N];
@@ -147,6 +154,8 @@ constexpr int kRowShr4 = 0x114;      // shift right by 4 within a row
 constexpr int kRowShr8 = 0x118;      // shift right by 8 within a row
 constexpr int kRowBcast15 = 0x142;   // lane 15 of each row -> next row
 constexpr int kRowBcast31 = 0x143;   // lane 31 -> rows 2 and 3
+constexpr int kWaveShl1 = 0x130;     // lane l receives lane l + 1 (lane 63 receives 0)
+constexpr int kWaveShr1 = 0x138;     // lane l receives lane l - 1 (lane 0 receives 0)
 
 // ---------------------------------------------------------------------------
 // Wavefront combine: 64 lane values -> one value, returned uniformly (SGPR

@@ -398,8 +398,6 @@ __device__ __forceinline__ void static_for_while(F&& f) {
 constexpr int kRing = 384;        // offsets entries held in LDS per wavefront
 constexpr int kCpolNT = 2;        // the nontemporal bit of a load's cache policy
 constexpr int kWaitLds = 0xC07F;  // s_waitcnt lgkmcnt(0): LDS reads returned, other counters free
-constexpr int kWaveShl1 = 0x130;  // DPP wave_shl:1: lane l receives lane l + 1 (lane 63 receives 0)
-constexpr int kWaveShr1 = 0x138;  // DPP wave_shr:1: lane l receives lane l - 1 (lane 0 receives 0)
 
 struct RunLds {
   v4f tile[kWave * 4];   // one tile of up to 4 rows, swizzled

@@ -1,5 +1,5 @@
 // Iterative 1D Jacobi stencil: the time loop inside one persistent kernel
-// versus one kernel launch per step (gfx950).
+// versus one kernel launch per step, and many steps per launch (gfx950).
 //
 // Section VII-B of Zhang et al. points out a benefit of grid barriers that
 // the reduction does not show: a persistent kernel that holds the time loop
@@ -9,8 +9,8 @@
 //
 // The step is u'[i] = u[i] + r ((u[i-1] + u[i+1]) - 2 u[i]) for
 // 1 <= i <= n-2, with u[0] and u[n-1] fixed, each operation one binary32
-// operation in that order (no contraction), so both forms reproduce the
-// step-by-step definition bit for bit.
+// operation in that order (no contraction but one that rounds the same), so
+// every form reproduces the step-by-step definition bit for bit.
 //
 //   * relaunch:   k_jacobi_step per step, ping-pong between u and the
 //                 caller's scratch array;
@@ -25,7 +25,11 @@
 //                 its halo (device-scope atomic loads).  One barrier per K
 //                 steps; HBM is touched only at the start, at the end and for
 //                 the 2 K boundary values per workgroup and barrier.
+//   * blocked:    k_jacobi_tile advances windows held in single wavefronts
+//                 by up to hundreds of steps per launch, with no exchange
+//                 inside a launch; the form the library chooses by itself.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_prims.h"
 #include "internal.h"
@@ -183,6 +187,204 @@ __global__ __launch_bounds__(1024) void k_jacobi_persistent(StencilArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Blocked steps: many steps per launch on windows that live in one
+// wavefront's registers.
+//
+// One launch per step is bound by the 8 bytes per value that it moves, and
+// by the launch below about a million values; the persistent form by the
+// exchange through LDS and the workgroup barrier of every step.  Here a
+// wavefront loads a window of 64 V consecutive interior values and advances
+// it k steps with no exchange at all: lane l holds the V values from V l on,
+// the two values beside its run come from the adjacent lanes by DPP wave
+// shifts that fold into the additions that use them, and the k outermost
+// values on each side, which go stale one per step, are recomputed by the
+// neighbouring windows.  The kernel boundary is the only synchronization, so
+// nothing has to be co-resident and any length runs.  What bounds it is VALU
+// issue: 4 operations per value and step (5 in the method, see FMA below)
+// at 3.0 to 3.3 cycles each with two or more wavefronts per SIMD, 4.2 with
+// one.
+// ---------------------------------------------------------------------------
+
+// One step on the window.  The neighbour sums run one value ahead of the
+// update, so it is in place without moves.
+//   FMA   the doubling and the subtraction are one fused operation, which
+//         rounds the same, since 2 c is exact, unless 2 c overflows;
+//   ENDS  the window may lie at an end of the interior: `left` holds the
+//         array's first value in lane 0 and `right` its last one in lane 63,
+//         lanes that the wave shifts do not write.
+template <int V, bool FMA, bool ENDS>
+__device__ __forceinline__ void window_step(float (&x)[V], float r, float& left, float& right) {
+#pragma clang fp contract(off)
+  float nb, nb_last;
+  if constexpr (ENDS) {
+    left = dpp_update<kWaveShr1>(left, x[V - 1]);
+    right = dpp_update<kWaveShl1>(right, x[0]);
+    nb = left + x[1];
+    nb_last = x[V - 2] + right;
+  } else {
+    nb = dpp_move<kWaveShr1, 0xF, 0xF>(x[V - 1]) + x[1];
+    nb_last = x[V - 2] + dpp_move<kWaveShl1, 0xF, 0xF>(x[0]);
+  }
+  // In groups of four values, with the compiler kept from moving operations
+  // between a group's four stages: each operation's operands are then at
+  // least four operations old (a result takes two issue slots), which the
+  // compiler's own order does not keep to (24 M values, 64 steps with
+  // V = 16: 130 us against 177).  Windows of up to 8 values per lane run
+  // one wavefront per SIMD and are left to the compiler (64 K values, V = 4:
+  // 69 us against 74 for 1000 steps).
+  constexpr int G = V > 8 ? 4 : V;
+  auto fence = [] {
+    if constexpr (V > 8) __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int g = 0; g < V; g += G) {
+    float d[G];
+    d[0] = nb;
+#pragma unroll
+    for (int i = g + 1; i < g + G; ++i) d[i - g] = i + 1 < V ? x[i - 1] + x[i + 1] : nb_last;
+    if (g + G < V) nb = x[g + G - 1] + x[g + G + 1];
+    fence();
+#pragma unroll
+    for (int i = g; i < g + G; ++i) {
+      if constexpr (FMA)
+        d[i - g] = __builtin_fmaf(-2.0f, x[i], d[i - g]);
+      else
+        d[i - g] = d[i - g] - 2.0f * x[i];
+    }
+    fence();
+#pragma unroll
+    for (int i = g; i < g + G; ++i) d[i - g] = r * d[i - g];
+    fence();
+#pragma unroll
+    for (int i = g; i < g + G; ++i) x[i] = x[i] + d[i - g];
+    fence();
+  }
+}
+
+// `steps` steps on the window.  The fused form rounds as the method's five
+// operations do while no doubling overflows: for 0 <= r <= 1/2 a step
+// enlarges the largest magnitude by rounding only (by less than 2^-20 of
+// it), so from below 2^100 none overflows in 2^24 steps.  Other values (NaN
+// and infinities among them) take the five operations.
+template <int V>
+__device__ __forceinline__ void window_steps(float (&x)[V], int steps, float r, float left, float right, bool ends) {
+  bool small = __builtin_fabsf(left) < 0x1p100f && __builtin_fabsf(right) < 0x1p100f;
+#pragma unroll
+  for (int i = 0; i < V; ++i) small = small && __builtin_fabsf(x[i]) < 0x1p100f;  // false for NaN
+  // r in a vector register: with two or more wavefronts per SIMD a
+  // multiplication by a scalar register issues at half the rate (4.1 against
+  // 2.1 cycles).
+  const bool fma = r >= 0.0f && r <= 0.5f && steps <= (1 << 24) && __ballot(!small) == 0;
+  asm volatile("" : "+v"(r));
+  auto loop = [&](auto f, auto e) {
+    constexpr bool F = decltype(f)::value, EN = decltype(e)::value;
+    constexpr int U = 4;  // steps per loop iteration
+    int s = 0;
+    for (; s + U <= steps; s += U) {
+#pragma unroll
+      for (int q = 0; q < U; ++q) window_step<V, F, EN>(x, r, left, right);
+    }
+    for (; s < steps; ++s) window_step<V, F, EN>(x, r, left, right);
+  };
+  if (fma && !ends)
+    loop(std::true_type{}, std::false_type{});
+  else if (fma)
+    loop(std::true_type{}, std::true_type{});
+  else
+    loop(std::false_type{}, std::true_type{});
+}
+
+constexpr int kTileWG = 256;  // four wavefronts, one per SIMD; they do not cooperate
+
+// Lane l's V values from p + V l on, by the widest loads that the array's
+// alignment (4 bytes) and V allow.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float v2f_any __attribute__((ext_vector_type(2), aligned(4)));
+
+template <int V>
+__device__ __forceinline__ void load_window(float (&x)[V], const float* p) {
+  if constexpr (V % 4 == 0) {
+#pragma unroll
+    for (int i = 0; i < V; i += 4) {
+      const v4f_any v = *reinterpret_cast<const v4f_any*>(p + i);
+      x[i] = v.x, x[i + 1] = v.y, x[i + 2] = v.z, x[i + 3] = v.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; i += 2) {
+      const v2f_any v = *reinterpret_cast<const v2f_any*>(p + i);
+      x[i] = v.x, x[i + 1] = v.y;
+    }
+  }
+}
+
+// Stores the values of the lane's run [j0, j0 + V) that lie in [a, b).
+template <int V>
+__device__ __forceinline__ void store_window(const float (&x)[V], float* p, int j0, int a, int b) {
+  constexpr int C = V % 4 == 0 ? 4 : 2;
+#pragma unroll
+  for (int i = 0; i < V; i += C) {
+    const int j = j0 + i;
+    if (j >= a && j + C <= b) {
+      if constexpr (C == 4)
+        *reinterpret_cast<v4f_any*>(p + i) = v4f_any{x[i], x[i + 1], x[i + 2], x[i + 3]};
+      else
+        *reinterpret_cast<v2f_any*>(p + i) = v2f_any{x[i], x[i + 1]};
+    } else if (j + C > a && j < b) {
+#pragma unroll
+      for (int e = 0; e < C; ++e)
+        if (j + e >= a && j + e < b) p[i + e] = x[i + e];
+    }
+  }
+}
+
+// Wavefront w advances the interior values [w m, (w + 1) m) (element 1 + i
+// of the array is interior value i, of N) by `steps` <= k steps from src to
+// dst.  Its window of 64 V values starts k before them, moved inward where
+// it would leave the interior (N >= 64 V).
+template <int V>
+__global__ __launch_bounds__(kTileWG) void k_jacobi_tile(const float* __restrict__ src, float* __restrict__ dst,
+                                                         int64_t N, int m, int k, int steps, float r) {
+  constexpr int W = kWave * V;
+  const int64_t w = (int64_t)blockIdx.x * (kTileWG / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int64_t lo = w * m;
+  if (lo >= N) return;
+  const int64_t hi = std::min(lo + m, N);
+  const int64_t base = std::min(std::max<int64_t>(lo - k, 0), N - W);
+  const int lane = __lane_id();
+  const int j0 = V * lane;
+  float x[V];
+  load_window<V>(x, src + 1 + base + j0);
+  const float left = src[base], right = src[1 + base + W];
+  window_steps<V>(x, steps, r, left, right, base == 0 || base + W == N);
+  store_window<V>(x, dst + 1 + base + j0, j0, (int)(lo - base), (int)(hi - base));
+  if (lo == 0 && lane == 0) dst[0] = left;
+  if (hi == N && lane == 0) dst[N + 1] = right;
+}
+
+// The whole interior (N <= 64 V values) in one wavefront, in place: the
+// values at and past its end keep what they hold.
+template <int V>
+__global__ __launch_bounds__(kWave) void k_jacobi_one_window(float* u, int N, int steps, float r) {
+  const int j0 = V * (int)__lane_id();
+  float x[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) x[i] = j0 + i <= N ? u[1 + j0 + i] : 0.0f;  // position N: the array's last value
+  float left = u[0], right = u[N + 1];
+  for (int s = 0; s < steps; ++s) {
+    float y[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) y[i] = x[i];
+    window_step<V, false, true>(y, r, left, right);
+#pragma unroll
+    for (int i = 0; i < V; ++i) x[i] = j0 + i < N ? y[i] : x[i];
+  }
+#pragma unroll
+  for (int i = 0; i < V; ++i)
+    if (j0 + i < N) u[1 + j0 + i] = x[i];
+}
+
 namespace {
 
 const void* persistent_kernel(int vpt) {
@@ -207,12 +409,144 @@ int stencil_coresident(int vpt, int wg, const DeviceInfo& dev, int* n_wg) {
   return RED_OK;
 }
 
+// Shapes of the blocked-step form: windows of 64 V values.
+struct TileKernel {
+  int v;
+  const void* fn;
+};
+const TileKernel kTileKernels[] = {
+    {2, reinterpret_cast<const void*>(&k_jacobi_tile<2>)},   {4, reinterpret_cast<const void*>(&k_jacobi_tile<4>)},
+    {6, reinterpret_cast<const void*>(&k_jacobi_tile<6>)},   {8, reinterpret_cast<const void*>(&k_jacobi_tile<8>)},
+    {12, reinterpret_cast<const void*>(&k_jacobi_tile<12>)}, {16, reinterpret_cast<const void*>(&k_jacobi_tile<16>)},
+    {20, reinterpret_cast<const void*>(&k_jacobi_tile<20>)}, {24, reinterpret_cast<const void*>(&k_jacobi_tile<24>)},
+    {28, reinterpret_cast<const void*>(&k_jacobi_tile<28>)}, {36, reinterpret_cast<const void*>(&k_jacobi_tile<36>)},
+};
+
+// One wavefront for the whole array: up to 64 x 8 interior values.
+struct OneWindowKernel {
+  int v;
+  double us_per_step;  // measured
+  const void* fn;
+};
+const OneWindowKernel kOneWindowKernels[] = {
+    {2, 0.044, reinterpret_cast<const void*>(&k_jacobi_one_window<2>)},
+    {4, 0.064, reinterpret_cast<const void*>(&k_jacobi_one_window<4>)},
+    {8, 0.104, reinterpret_cast<const void*>(&k_jacobi_one_window<8>)},
+};
+
+struct TilePlan {
+  const void* fn = nullptr;
+  int launches = 0;  // 1: the one-window kernel; else even, u and scratch alternating
+  int k = 0;         // window margin: at least the steps of one launch
+  int m = 0;         // interior values that a window advances
+  int64_t waves = 0;
+};
+
+// Cost of a launch besides its steps: the kernel boundary, the ramp and the
+// first load (2.2 us from 1 K to 64 K values), and the array's read and
+// write.  While every wavefront is resident at once all of them load before
+// they compute (about 10 TB/s beyond the 2.2 us, from the caches); beyond
+// that the loads run under other wavefronts' steps at a large copy's rate,
+// 4.8 TB/s (24 M values, 4 steps: 40 us), less for runs longer than 64 bytes
+// per lane, whose loads and stores touch more lines at a time.
+constexpr double kTileLaunchUs = 2.2;
+constexpr double kTileCachedBytesPerUs = 10e6;
+constexpr double kTileStreamBytesPerUs = 4.8e6;
+
+// Cycles per VALU operation and SIMD with w wavefronts resident on it
+// (measured: 4 M and 1 M values with windows of 12 to 36 values per lane).
+double tile_cycles_per_op(double w) { return w <= 1 ? 4.6 : w <= 2 ? 3.2 : w <= 3 ? 2.9 : 2.75; }
+
+// The shape of the lowest modelled time for N interior values and `steps`
+// steps.  More steps per launch save launches and widen the recomputed
+// margins; a larger window has relatively narrower margins, but a small
+// array then leaves SIMDs idle, and a step takes as long as the fullest SIMD
+// (4 V operations per wavefront on it).
+TilePlan plan_tiles(int64_t N, int steps, const DeviceInfo& dev) {
+  TilePlan best;
+  double best_us = 1e300;
+  if (N <= 8 * kWave)
+    for (const OneWindowKernel& k : kOneWindowKernels)
+      if (N <= (int64_t)k.v * kWave) {
+        best.fn = k.fn;
+        best.launches = 1;
+        best_us = kTileLaunchUs + k.us_per_step * steps;
+        break;
+      }
+  const double cyc_us = dev.clock_khz * 1e-3;
+  for (const TileKernel& t : kTileKernels) {
+    const int w_vals = kWave * t.v;
+    if (N < w_vals) break;
+    // From the fewest launches whose margins leave a quarter of the window,
+    // up in steps of about a third, eight candidates.
+    int64_t L = std::max<int64_t>(2, (steps + 24 * t.v - 1) / (24 * t.v));
+    for (int c = 0; c < 8; ++c) {
+      L += L & 1;
+      const int per = (int)((steps + L - 1) / L);
+      const int k = (per + 3) & ~3;  // keeps the block edges of interior windows on whole vectors
+      const int m = w_vals - 2 * k;
+      const int64_t waves = (N + m - 1) / m;
+      const int64_t wgs = (waves + kTileWG / kWave - 1) / (kTileWG / kWave);
+      const bool resident = wgs <= 8 * (int64_t)dev.cus;
+      const double load = resident ? (double)((wgs + dev.cus - 1) / dev.cus) : (double)wgs / dev.cus + 0.5;
+      const double step_us = per * load * (4 * t.v + 2) * tile_cycles_per_op(load) / cyc_us;
+      double us;
+      if (resident) {
+        us = step_us + 8.0 * (double)N / kTileCachedBytesPerUs;
+      } else {
+        const double mem_us = 8.0 * (double)N / kTileStreamBytesPerUs * (t.v <= 16 ? 1.0 : t.v <= 20 ? 1.15 : 1.35);
+        us = std::max(step_us, mem_us) + 0.2 * std::min(step_us, mem_us);
+      }
+      us = (double)L * (us + kTileLaunchUs);
+      if (us < best_us) {
+        best_us = us;
+        best = TilePlan{t.fn, (int)L, k, m, waves};
+      }
+      if (per <= 8) break;
+      L += std::max<int64_t>(2, L / 3);
+    }
+  }
+  return best;
+}
+
+int tile_launch(float* u, float* scratch, int64_t n, int steps, float r, hipStream_t s, const DeviceInfo& dev) {
+  int64_t N = n - 2;
+  TilePlan t = plan_tiles(N, steps, dev);
+  if (t.launches == 1) {
+    int n32 = (int)N;
+    void* args[] = {&u, &n32, &steps, &r};
+    return launch(t.fn, 1, kWave, args, s, false);
+  }
+  const int grid = (int)((t.waves + kTileWG / kWave - 1) / (kTileWG / kWave));
+  float* src = u;
+  float* dst = scratch;
+  for (int64_t i = 0; i < t.launches; ++i) {
+    int now = (int)(steps * (i + 1) / t.launches - steps * i / t.launches);
+    void* args[] = {&src, &dst, &N, &t.m, &t.k, &now, &r};
+    int rc = launch(t.fn, grid, kTileWG, args, s, false);
+    if (rc) return rc;
+    std::swap(src, dst);
+  }
+  return RED_OK;
+}
+
 }  // namespace
 
 int stencil_launch(float* u, float* scratch, int64_t n, int steps, float r, int steps_per_sync, const red_plan& p,
                    Workspace* ws, hipStream_t s, const DeviceInfo& dev) {
   if (n < 3 || steps == 0) return RED_OK;
   int variant = p.variant;
+  // AUTO without a workgroup size or grid of the caller's (which are shapes
+  // of the other forms): blocked steps.  At every size they were faster than
+  // both (1000 steps on 64 K values: 70 us against 200 for the persistent
+  // form; 200 steps on 4 M: 84 against 188; 40 steps on 24 M, which only
+  // one launch per step could run: 93 against 1220).
+  if (variant == RED_VARIANT_AUTO && p.wg == 0 && p.grid == 0) {
+    const int slot = timer_begin(s);
+    const int rc = tile_launch(u, scratch, n, steps, r, s, dev);
+    timer_end(s, slot);
+    return rc;
+  }
   // The geometry (workgroups, block length) is set for the caller's halo,
   // or for a halo of 8 when the library chooses it.
   const int k_req = steps_per_sync > 0 ? steps_per_sync : 8;

@@ -162,3 +162,44 @@ def test_runs_shorter_than_one_exchange_repeated(lib):
             for flags in (0, 16, 4):
                 got = run(lib, x, steps, 0.3, variant=PERSISTENT, flags=flags)
                 assert np.array_equal(got, want), (rep, steps, flags, np.flatnonzero(got != want)[:5])
+
+
+@pytest.mark.parametrize("n", [3, 66, 129, 130, 131, 258, 513, 514, 515, 1027, 4100, 20_011, 65_536, 200_003,
+                               1_000_003, 4_194_307, 24_000_001])
+def test_blocked_steps_bit_exact(lib, n):
+    """The library's own choice of form (AUTO): many steps per launch on
+    wavefront windows.  Sizes at the edges of the one-window kernel (up to
+    512 interior values) and of the window lengths, few and many steps (one
+    step, launches of unequal step counts, margins up to three quarters of a
+    window), misaligned arrays: bit for bit."""
+    x = inputs.normal_f32(n, sub=80)
+    cases = [(1, 0), (7, 1), (100, 3)] if n > 300_000 else [(1, 1), (2, 0), (9, 3), (131, 2), (1000, 0)]
+    for steps, shift in cases:
+        want = oracle.jacobi_1d_f32(x, steps, 0.3)
+        say("blocked steps", n, steps, shift)
+        got = run(lib, x, steps, 0.3, shift=shift)
+        assert np.array_equal(got, want), (n, steps, shift, np.flatnonzero(got != want)[:5])
+
+
+@pytest.mark.parametrize("r", [0.5, 0.25, 0.75, -0.3])
+def test_blocked_steps_extreme_values(lib, r):
+    """Values whose doubling overflows, infinities, NaN, subnormals and
+    signed zeros, and coefficients outside [0, 1/2]: the form that fuses
+    the doubling and the subtraction must not be taken where it would round
+    or overflow differently.  Bit patterns are compared with the form of one
+    launch per step (NaN by place)."""
+    n = 50_001
+    x = inputs.normal_f32(n, sub=81)
+    x[::7] *= np.float32(1e-39)
+    x[5::11] = -0.0
+    x[20_000:20_003] = np.float32(3.0e38)
+    x[20_010] = np.float32(-3.3e38)
+    x[30_000] = np.inf
+    x[40_000] = np.nan
+    x[0], x[-1] = np.float32(2.5e38), np.float32(-1e-40)
+    for steps in (1, 3, 40):
+        want = run(lib, x, steps, r, variant=RELAUNCH)
+        got = run(lib, x, steps, r)
+        nan = np.isnan(want)
+        assert np.array_equal(nan, np.isnan(got)), (r, steps)
+        assert np.array_equal(got.view(np.int32)[~nan], want.view(np.int32)[~nan]), (r, steps)
