@@ -185,10 +185,12 @@ int get_workspace(hipStream_t s, Workspace** out) {
     return set_error(RED_ENOMEM, "workspace allocation of %zu bytes failed: %s", kWorkspaceBytes,
                      hipGetErrorString(e));
   }
-  e = hipMemset(w.base, 0, kWorkspaceBytes);
+  // Cleared on the stream that will use it: a clear on the null stream is
+  // not ordered before the kernels of a non-blocking stream.
+  e = hipMemsetAsync(w.base, 0, kWorkspaceBytes, s);
   if (e != hipSuccess) {
     (void)hipFree(w.base);
-    return hip_fail(e, "hipMemset(workspace)");
+    return hip_fail(e, "hipMemsetAsync(workspace)");
   }
   char* p = static_cast<char*>(w.base);
   w.words = reinterpret_cast<BarrierWords*>(p);
