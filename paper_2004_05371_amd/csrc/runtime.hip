@@ -535,8 +535,8 @@ int red_check_error(void* stream) {
   for (const Line& g : hw.node) stale = stale || g.v || g.pad[0];
   if (!err && !stale) return RED_OK;
   // Clear the error and every barrier word (the barrier was abandoned).
-  RED_HIP(hipMemset(ws->words, 0, kWordsBytes));
-  RED_HIP(hipMemset(ws->seg_tickets, 0, kTicketBytes));
+  RED_HIP(hipMemsetAsync(ws->words, 0, kWordsBytes, s));
+  RED_HIP(hipMemsetAsync(ws->seg_tickets, 0, kTicketBytes, s));
   if (!err)
     return set_error(RED_ENOTSUP, "arrival counters were left incomplete (an abandoned barrier or ticket)");
   return set_error(RED_ETIMEOUT, "a grid-barrier watchdog fired on this stream");
