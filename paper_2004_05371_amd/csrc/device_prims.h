@@ -202,6 +202,18 @@ __device__ __forceinline__ void wave_segscan(double& v, int& f) {
   segscan_step<kRowBcast31, 0xC>(v, f);
 }
 
+// Inclusive sum across the wavefront (lane l: lanes 0 .. l), in the same
+// steps.
+__device__ __forceinline__ int wave_scan_add(int v) {
+  v += dpp_move<kRowShr1, 0xF, 0xF>(v);
+  v += dpp_move<kRowShr2, 0xF, 0xF>(v);
+  v += dpp_move<kRowShr4, 0xF, 0xF>(v);
+  v += dpp_move<kRowShr8, 0xF, 0xF>(v);
+  v += dpp_move<kRowBcast15, 0xA, 0xF>(v);
+  v += dpp_move<kRowBcast31, 0xC, 0xF>(v);
+  return v;
+}
+
 // ds_swizzle: xor butterfly (masks 1, 2, 4, 8, 16) inside each 32-lane half
 // (bit-mode pattern: and_mask = 0x1F, xor_mask in bits 14:10), then the two
 // half totals.

@@ -36,6 +36,7 @@
 // result is deterministic for a given grid and workgroup size, and the
 // three fix-ups give the same bits.
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "device_prims.h"
@@ -166,19 +167,29 @@ __device__ __forceinline__ bool seek_segment(const SegArgs& a, int64_t& s, int64
   return false;
 }
 
-// The segment that holds element lo of a non-empty slice, or for an empty
-// slice the first one that starts at or after lo: the first s in
-// [0, nseg] with offsets[s] >= lo by binary search (offsets[nseg] = E >= lo),
-// stepped back by one when segment s-1 crosses lo.
-__device__ __forceinline__ int64_t first_segment(const SegArgs& a, int64_t lo) {
-  int64_t L = 0, R = a.nseg;
-  while (L < R) {
-    const int64_t mid = (L + R) >> 1;
-    if (offset_at(a.offsets, mid) >= lo)
-      R = mid;
-    else
-      L = mid + 1;
+// The first s in [0, nseg] with offsets[s] >= pos (0 <= pos <= E =
+// offsets[nseg]), by one wavefront: 64 lanes probe at a time, so a batch of
+// two million segments takes 4 dependent loads and not 21.
+__device__ __forceinline__ int64_t first_at_or_after(const int64_t* offsets, int64_t nseg, int64_t pos) {
+  const int lane = __lane_id();
+  int64_t L = 0, R = nseg;  // the answer lies in [L, R]; offsets[R] >= pos
+  while (R - L > kWave) {
+    const int64_t d = R - L;
+    // Probe l at L + (l + 1) d / 64; the last one is R itself.
+    const bool below = offsets[L + (((int64_t)(lane + 1) * d) >> 6)] < pos;
+    const int c = __popcll(__ballot(below));  // probes 0 .. c-1 lie below; c < 64
+    R = L + (((int64_t)(c + 1) * d) >> 6);
+    if (c > 0) L = L + (((int64_t)c * d) >> 6) + 1;
   }
+  const bool below = L + lane < R && offsets[L + lane] < pos;
+  return L + __popcll(__ballot(below));
+}
+
+// The segment that holds element lo of a non-empty slice, or for an empty
+// slice the first one that starts at or after lo: the first s with
+// offsets[s] >= lo, stepped back by one when segment s-1 crosses lo.
+__device__ __forceinline__ int64_t first_segment(const SegArgs& a, int64_t lo) {
+  const int64_t L = first_at_or_after(a.offsets, a.nseg, lo);
   return (L > 0 && offset_at(a.offsets, L) > lo) ? L - 1 : L;
 }
 
@@ -239,9 +250,11 @@ constexpr int64_t kWaveSliceMeanLen = 16384;
 
 // Batches whose mean segment holds fewer values than this take the
 // reduce-by-key form of the wavefront slices (plans of at most 4 loads per
-// thread).  Measured on MI355X with 2^28 values, 512 x 4, two workgroups
-// per CU: 4.7 TB/s against 0.9 per piece at 64 values, 5.7 against 5.0 at
-// 512, even at 1024.
+// thread).  Measured on MI355X with 60 M values, 256 x 4, four workgroups
+// per CU, us per call against one combine per piece: equal segments of 512
+// values 52.7 against 62.0, of 1024 49.8 against 48.5; of random length
+// (mean 512) 52.4 against 72.8, (mean 1024) 50.1 against 53.8, (mean 2048)
+// 49.0 against 47.5.
 constexpr int64_t kRunsMeanLen = 1024;
 
 // Wavefront-granular slices (short segments: every wave walks its own
@@ -351,67 +364,51 @@ __device__ __forceinline__ void seg_wave_slices(const SegArgs& a) {
   }
 }
 
-// f(integral_constant<B>), ..., f(integral_constant<E - 1>); the _while
-// form stops after the first call that returns false.
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for_while(F&& f) {
-  if constexpr (B < E) {
-    if (f(std::integral_constant<int, B>{})) static_for_while<B + 1, E>(f);
-  }
-}
-
-// Reduce-by-key form of the wavefront slices, for very short segments.
+// Reduce-by-key form of the wavefront slices, for short segments of any mix
+// of lengths.
 //
-// Each tile of 64 x IPT 16-byte vectors (256 IPT contiguous values) is
-// walked in parts of RS rows (fewer rows when the mean segment is short),
-// and in each part lane l holds the run of RL = 4 RS consecutive values
-// that starts at value RL l of the part.  The tile comes into LDS by
-// direct-to-LDS loads, each lane fetching the vector that the run reads
-// expect at its position, so the loads hold no registers while in flight;
-// a part's rows are loaded for the next tile as soon as the part has been
-// read.  The starts of the segments that follow the open one come from a
-// ring of the offsets held in LDS (kRing entries ahead of the walk,
-// refilled a tile ahead).  When fewer than 64 segments start in a part and
-// no run holds two starts:
-//   * each lane sums its run in binary64, cut at the start it holds (if
-//     any) into a head, the end of the segment open on its left, and a
-//     tail;
-//   * a segmented inclusive scan of the tails in binary64 across the lanes,
-//     seeded with the slice's partial of the open segment, gives every lane
-//     the partial of the segment open at its right end;
-//   * a lane that holds a start completes the segment that ends there (its
-//     head plus the scan of the lane on its left): it writes the sum when
-//     the segment began in the part, and the first start of the part
-//     closes the segment that was open, which may have begun before the
-//     slice and goes through finish_piece.
-// Other parts (an empty segment, two starts in one run, 64 starts or more)
-// and the rest of their tile are finished piece by piece as in
-// seg_wave_slices, the open partial carried in binary64 between the two.
-constexpr int kRing = 384;        // offsets entries held in LDS per wavefront
-constexpr int kCpolNT = 2;        // the nontemporal bit of a load's cache policy
-constexpr int kWaitLds = 0xC07F;  // s_waitcnt lgkmcnt(0): LDS reads returned, other counters free
-
+// Each tile of 64 x ROWS 16-byte vectors (256 ROWS contiguous values) comes
+// in by coalesced loads, one tile ahead, and is turned over in LDS so that
+// lane l holds the run of RL = 4 ROWS consecutive values from RL l on.  Then
+//   * 64 offsets at a time, lane k takes the segment q + k that starts in the
+//     tile: a non-empty one sets the bit of its start in a mask word per
+//     run, and its rank among the tile's non-empty segments is its place in
+//     the ballot;
+//   * each lane adds up its run in binary64; at a start it puts the sum so
+//     far in LDS (where the tile was) at the start's rank and begins again,
+//     so a run may hold any number of starts;
+//   * a segmented scan of what is left at the runs' ends gives each lane the
+//     partial of the segment open at its left edge, which it adds to the sum
+//     at its first start;
+//   * the sum at rank j + 1 belongs to the segment of rank j: the lanes that
+//     took the segments write them out in their order, 64 neighbouring sums
+//     at a time, and 0 for the empty ones.
+// The sum at rank 0 closes the segment that was open before the tile, which
+// may have begun before the slice and then goes through finish_piece.  A
+// tile without a start adds to per-lane sums of the open segment and needs
+// no scan.  A tile with more starts than its LDS holds sums (half its
+// values) is walked in two halves, which cannot.
+//
+// What bounds it below about 64 values per segment is instruction issue: per
+// row of 64 values about 10 operations, and about 250 per tile, which is
+// why the runs are as long as four wavefronts per SIMD have registers for;
+// above, the reading of the values.  The walk it replaced finished every
+// tile with an empty segment, or with two starts in one run, piece by piece,
+// bound by the chain of dependent steps of each piece.  64 M values, us per
+// call now and before: segments of random length (empty ones among them) of
+// mean 4 118 / 3631, 16 69 / 1148, 64 59 / 402, 512 54 / 64; equal lengths
+// of 4 114 / 2864, 16 66 / 72, 64 56 / 61, 512 52 / 57.
+template <int ROWS>
 struct RunLds {
-  v4f tile[kWave * 4];   // one tile of up to 4 rows, swizzled
-  unsigned slot[kWave];  // per lane run: (k + 1) << 16 | tile position of start k, or 0
-  int64_t ring[kRing];   // offsets[i] at i mod kRing, for i in [fill - kRing, fill)
+  v4f tile[kWave * ROWS * 9 / 8];  // one tile of up to ROWS rows, padded; then sums by rank
+  unsigned mask[kWave];            // per lane run: bit i set when a segment starts at its value i
 };
 
-// LDS words written by one lane and read by another inside a wavefront.
-// The wavefront's LDS instructions execute in program order, so ordinary
-// LDS loads and stores suffice; the accesses are relaxed atomics on
-// LDS-space pointers (no compiler may forward a lane's own store to its
-// load, as it could for plain data) behind compiler-only fences (keeping
-// program order).  A volatile access through a generic pointer would be
-// compiled as a flat access with a wait for every outstanding global load.
+constexpr int kChunks = 4;  // chunks of 64 offsets loaded a tile ahead
+
+// The wavefront's LDS instructions execute in program order, so words that
+// one lane writes and another reads need no wait, only an order that the
+// compiler keeps.
 template <class T>
 using LdsPtr = __attribute__((address_space(3))) T*;
 
@@ -420,80 +417,293 @@ __device__ __forceinline__ LdsPtr<T> lds_ptr(T* p) {
   return (LdsPtr<T>)p;
 }
 
-template <class T>
-__device__ __forceinline__ void lds_put(LdsPtr<T> p, int i, T v) {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __atomic_store_n(p + i, v, __ATOMIC_RELAXED);
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-template <class T>
-__device__ __forceinline__ T lds_get(LdsPtr<T> p, int i) {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  const T v = __atomic_load_n(p + i, __ATOMIC_RELAXED);
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  return v;
+// Place in the tile buffer of the tile's vector i: one vector of padding
+// after every 8, so that the run reads (lane l, vector ROWS l + j) of
+// neighbouring lanes fall in distinct banks, as do the writes of a row, and
+// every read and write of a lane lies at a fixed distance from its first.
+__device__ __forceinline__ constexpr int run_place(int i) { return i + (i >> 3); }
+
+// Lanes of the ballot b below the calling one.
+__device__ __forceinline__ int lanes_below(uint64_t b) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
 }
 
-// The same accesses while a direct-to-LDS load fills another LDS region.
-// The compiler cannot tell the regions apart, so before any LDS access it
-// would wait for every load in flight.  Written as inline assembly, which
-// its wait insertion does not treat as a memory access, each access waits
-// only for itself (lgkmcnt(0) in the same block, so no register is read or
-// reused before the LDS has answered).
-template <class T>
-__device__ __forceinline__ unsigned lds_addr(LdsPtr<T> p, int i) {
-  return (unsigned)(uintptr_t)(p + i);
+// offsets[i] and offsets[i + 1] in one load (offsets are 8-byte aligned).
+typedef long long v2l __attribute__((ext_vector_type(2), aligned(8)));
+
+// The slice [lo, hi) of wavefront w, by tiles of ROWS rows.
+template <int ROWS, bool NT, int FIX>
+__device__ __forceinline__ void seg_walk_runs(const SegArgs& a, const LdsPtr<v4f> tile, const LdsPtr<unsigned> mask,
+                                              int64_t w, int64_t chunk, int64_t lo, int64_t hi, int64_t E,
+                                              bool end_slice, int64_t& own_fix) {
+  static_assert(ROWS <= 8, "runs of at most 32 values");
+  const LdsPtr<double> sums = (LdsPtr<double>)tile;
+  const int lane = __lane_id();
+  const int nseg = (int)a.nseg;  // below 2^31
+  const int shift = (int)((reinterpret_cast<uintptr_t>(a.x) & 15) >> 2);
+  const v4f* xa = reinterpret_cast<const v4f*>(a.x - shift);
+  const int64_t vlo = (lo + shift) >> 2;
+  const int64_t vhi = (hi + shift + 3) >> 2;  // vectors [vlo, vhi) hold the slice
+  constexpr int64_t T = kWave * ROWS;
+  const int64_t ntiles = lo < hi ? (vhi - vlo + T - 1) / T : 0;
+  // Past the slice's last vector that vector is read again (its values lie
+  // at or past hi there and are masked out): one path and one place in the
+  // loop, so that the loads go straight to the registers that the next
+  // tile is taken from (where paths meet, a register that a load is still
+  // to fill is copied, which waits for the load).
+  v4f cur[ROWS];
+  auto load_tile = [&](int64_t t) {
+    const int64_t v0 = vlo + t * T + lane;
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) cur[u] = load_vec<NT>(xa + std::min(v0 + u * kWave, vhi - 1));
+  };
+  if (ntiles > 0) load_tile(0);
+
+  // q: the first segment that starts at or after the position reached.
+  // so: the non-empty segment open there (-1: none), which began before
+  // the slice if `cut`; its sum so far is Cs, plus the sum of cl over the
+  // lanes if `spread`.
+  int q = (int)first_at_or_after(a.offsets, nseg, lo);
+  double Cs = 0.0, cl = 0.0;
+  bool spread = false;
+
+  // Entry c 64 + lane from q on: its start and the next one's (past the
+  // last segment, the last segment's again: take() tells by the count).
+  auto entry = [&](int at, int c) -> v2l {
+    const int i = std::min(c * kWave + lane, nseg - at - 1);
+    return *reinterpret_cast<const v2l*>(a.offsets + at + i);
+  };
+  // Chunks loaded ahead: as many as the mean segment length makes a tile
+  // need (further ones are loaded when they turn out to be needed).
+  const int ahead = (int)std::min<int64_t>(
+      kChunks, 1 + (4 * T * nseg / std::max<int64_t>(E, 1) + kWave / 2) / kWave);
+  v2l ent[kChunks];
+  auto load_entries = [&]() {
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c)
+      if (c < ahead) ent[c] = entry(q, c);
+  };
+  if (ntiles > 0) load_entries();
+  mask[lane] = 0u;
+  // Every load completes before the stores that follow it are issued, on
+  // every path: with loads and stores pending together the compiler can
+  // only wait for all of them.
+  auto loads_done = [] { __builtin_amdgcn_s_waitcnt(0); };
+  loads_done();
+  // The segment before q crosses lo unless q starts there.
+  int so = ntiles > 0 && q > 0 && (q == nseg || read_lane(ent[0].x, 0) > lo) ? q - 1 : -1;
+  bool cut = so >= 0;
+
+  // Walks the part of the tile that starts at value f0 and whose run values
+  // are xv; returns false, with nothing changed, when it holds too many
+  // starts for LDS.
+  auto part = [&](auto rl_tag, const float* xr, int64_t f0) -> bool {
+    constexpr int RL = decltype(rl_tag)::value;
+    const int64_t f1 = f0 + (int64_t)kWave * RL;
+    const int64_t fe = std::min(f1, hi);
+    if (f0 >= hi) return true;
+
+    // The segments that start in the part, by chunks of 64: R non-empty
+    // ones, cnt in all, the last non-empty one s_last.
+    int R = 0, cnt = 0, s_last = 0;
+    // Rank of the lane's segment: -1 not in the part, -2 empty.  Returns
+    // whether the next chunk may hold more.
+    auto take = [&](v2l e, int s0, int& rank) -> bool {
+      const bool in = e.x < fe && lane < nseg - s0;
+      const bool full = in && e.y != e.x;
+      const uint64_t b = __ballot(full);
+      const int r = R + lanes_below(b);
+      rank = in ? (full ? r : -2) : -1;
+      if (full) {
+        const unsigned p = (unsigned)e.x - (unsigned)f0;
+        __hip_atomic_fetch_or(mask + p / RL, 1u << (p % RL), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      }
+      s_last = b ? s0 + 63 - __builtin_clzll(b) : s_last;
+      R += __popcll(b);
+      const int n = __popcll(__ballot(in));
+      cnt += n;
+      return n == kWave;
+    };
+    int rank[kChunks];
+    bool more = true;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      rank[c] = -1;
+      if (more && c < ahead) more = take(ent[c], q + c * kWave, rank[c]);
+    }
+    const int R_ahead = R, cnt_ahead = cnt;
+    while (more) {
+      v2l e[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) e[c] = entry(q + cnt, c);
+      const int s0 = q + cnt;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        int unused;
+        if (more) more = take(e[c], s0 + c * kWave, unused);
+      }
+      __builtin_amdgcn_s_waitcnt(0);  // those not taken, so that no later use of the registers waits
+    }
+    wave_order();
+    const unsigned word = mask[lane];
+    mask[lane] = 0u;
+    wave_order();
+    if constexpr (RL == 4 * ROWS)
+      if (R > 2 * kWave * ROWS) return false;
+    const int q0 = q;
+    q += cnt;
+    load_entries();
+
+    float xv[RL];
+#pragma unroll
+    for (int i = 0; i < RL; ++i) xv[i] = xr[i];
+    if (f0 < lo || f1 > hi) {  // values outside the slice are not its own
+      const int64_t p = f0 + (int64_t)RL * lane;
+#pragma unroll
+      for (int i = 0; i < RL; ++i) xv[i] = (p + i >= lo && p + i < hi) ? xv[i] : 0.0f;
+    }
+    if (R == 0) {
+#pragma unroll
+      for (int i = 0; i < RL; ++i) cl += (double)xv[i];
+      spread = true;
+      loads_done();
+      return true;
+    }
+    if (spread) {
+      Cs += wave_reduce_dpp<OpF64>(cl);
+      cl = 0.0;
+      spread = false;
+    }
+    const int own = __popc(word);
+    const LdsPtr<double> first = sums + (wave_scan_add(own) - own);  // the lane's first start
+    LdsPtr<double> at = first;
+    double acc = lane == 0 ? Cs : 0.0;  // the open segment enters with the first run
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+      if (word & (1u << i)) {
+        *at++ = acc;
+        acc = 0.0;
+      }
+      acc += (double)xv[i];
+    }
+    int f = word != 0u;
+    wave_segscan(acc, f);
+    const double left = dpp_move<kWaveShr1, 0xF, 0xF>(acc);  // lane - 1's scan; 0 in lane 0
+    if (word != 0u) *first = left + *first;
+    Cs = read_lane(acc, kWave - 1);
+    wave_order();
+
+    // Results.
+    loads_done();
+    if (so >= 0) {
+      if (!cut) {
+        if (lane == 0) a.out[so] = sums[0];
+      } else {
+        finish_piece<FIX>(a, so, offset_at(a.offsets, so), offset_at(a.offsets, so + 1), sums[0], lo, hi, w, chunk,
+                          &own_fix);
+      }
+    }
+    so = s_last;
+    cut = false;
+    auto put = [&](int s0, int rk) {
+      if (rk != -1 && rk + 1 < R) {
+        const double v = sums[std::max(rk + 1, 0)];
+        a.out[s0 + lane] = rk >= 0 ? v : 0.0;
+      }
+    };
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c)
+      if (c < ahead) put(q0 + c * kWave, rank[c]);
+    if (cnt > cnt_ahead) {  // the chunks beyond: their ranks again
+      int Rc = R_ahead;
+      for (int d = cnt_ahead; d < cnt; d += kWave) {
+        const v2l e = entry(q0 + d, 0);
+        const bool in = e.x < fe && lane < nseg - (q0 + d), full = in && e.y != e.x;
+        const uint64_t b = __ballot(full);
+        put(q0 + d, in ? (full ? Rc + lanes_below(b) : -2) : -1);
+        Rc += __popcll(b);
+      }
+    }
+    wave_order();
+    return true;
+  };
+
+  // Batches whose mean segment is under 2.25 values are walked in halves
+  // from the start.
+  const bool dense = 4 * E < 9 * (int64_t)nseg;
+  constexpr int RL = 4 * ROWS, RH = 2 * ROWS;  // values per lane run of a tile, of a half
+  for (int64_t t = 0; t < ntiles; ++t) {
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) tile[run_place(u * kWave) + run_place(lane)] = cur[u];
+    wave_order();
+    load_tile(t + 1);
+    const int64_t e0 = 4 * (vlo + t * T) - shift;
+    float xr[RL];
+    // The lane's run of `rows` vectors in the half (or whole) tile whose
+    // first vector is i0, to xr[at ..].
+    auto read_runs = [&](auto rows_tag, int i0, int at) {
+      constexpr int N = decltype(rows_tag)::value;
+      const LdsPtr<v4f> run = tile + run_place(i0) + run_place(N * lane);
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const v4f y = run[j];
+        xr[at + 4 * j] = y.x, xr[at + 4 * j + 1] = y.y, xr[at + 4 * j + 2] = y.z, xr[at + 4 * j + 3] = y.w;
+      }
+    };
+    bool done = false;
+    if (!dense) {
+      read_runs(std::integral_constant<int, ROWS>{}, 0, 0);
+      wave_order();
+      done = part(std::integral_constant<int, RL>{}, xr, e0);
+    }
+    if (!done) {
+      read_runs(std::integral_constant<int, ROWS / 2>{}, 0, 0);
+      read_runs(std::integral_constant<int, ROWS / 2>{}, kWave * ROWS / 2, RH);
+      wave_order();
+      part(std::integral_constant<int, RH>{}, xr, e0);
+      part(std::integral_constant<int, RH>{}, xr + RH, e0 + kWave * RH);
+    }
+    wave_order();
+  }
+  if (so >= 0) {  // the segment open at the slice's end ends at or after hi
+    if (spread) Cs += wave_reduce_dpp<OpF64>(cl);
+    finish_piece<FIX>(a, so, offset_at(a.offsets, so), offset_at(a.offsets, so + 1), Cs, lo, hi, w, chunk, &own_fix);
+  }
+  if (end_slice)  // the empty segments at E
+    for (int64_t i = (int64_t)q + lane; i < nseg; i += kWave) a.out[i] = 0.0;
 }
 
-__device__ __forceinline__ void lds_put_u32_now(LdsPtr<unsigned> p, int i, unsigned v) {
-  asm volatile("ds_write_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : : "v"(lds_addr(p, i)), "v"(v) : "memory");
-}
+// Slices of at least this many values: below, more wavefronts do not shorten
+// a call, and shorter slices cut more segments (1 M values in segments of
+// about 200: 8.4 us per call against 10.0 with slices down to 64).
+constexpr int64_t kRunsMinChunk = 512;
 
-__device__ __forceinline__ unsigned lds_get_u32_now(LdsPtr<unsigned> p, int i) {
-  unsigned v;
-  asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_addr(p, i)) : "memory");
-  return v;
-}
+// Rows of the largest tile.  The wide kernels keep 16 wavefronts per CU (125
+// VGPRs with 8 rows), the others 20 and more; the host takes a wide one for a
+// grid that is then wholly resident.
+constexpr int runs_max_rows(int ipt, bool wide) { return ipt == 4 ? (wide ? 8 : 4) : ipt == 2 && wide ? 4 : 2; }
 
-__device__ __forceinline__ int64_t lds_get_i64_now(LdsPtr<int64_t> p, int i) {
-  int64_t v;
-  asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_addr(p, i)) : "memory");
-  return v;
-}
-
-// Position in the tile buffer of the part's vector i (parts of RS rows):
-// within each group of 16 vectors the low bits are XOR-ed so that the run
-// reads (lane l, vector RS l + j) of 16 consecutive lanes fall in distinct
-// 16-byte bank groups.  The map is its own inverse and keeps each vector in
-// its row, so the load that fills position 64 u + l fetches vector
-// run_swz(64 u + l) and each load instruction still reads one contiguous
-// KB.
-template <int RS>
-__device__ __forceinline__ int run_swz(int i) {
-  return i ^ ((i >> 4) & (RS - 1));
-}
-
-// The values and the wavefront's three LDS regions come in as distinct
-// restrict pointers: the compiler then knows that the ring and slot
-// accesses cannot touch the tile that a direct-to-LDS load is filling, and
-// does not wait for that load before them.
-template <int IPT, bool NT, int FIX>
-__device__ static void seg_wave_runs_in(const SegArgs& a, const float* __restrict__ x,
-                                        const LdsPtr<v4f> __restrict__ tile,
-                                                 const LdsPtr<unsigned> __restrict__ slot,
-                                                 const LdsPtr<int64_t> __restrict__ ring) {
+// Tiles of 8 rows (2048 values) for slices of more than 4096 values, so that
+// a tile's fixed work is spread over more values (64 M values in segments of
+// 64: 56 us against 63 with 4 rows); 4 rows below, so that a short slice is
+// still two tiles or more and one loads while the other is walked (8 M
+// values: 15.6 us against 16.9 with 8 rows); 2 rows for slices of 512.
+template <int MAX_ROWS, bool NT, int FIX>
+__device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds<MAX_ROWS>* lds_all) {
   // Barrier fix-up: thread 0 holds the barrier generation of this launch.
   unsigned gen = FIX == kFixBarrier ? grid_barrier_gen(a.words) : 0u;
-  static_assert(IPT <= 4, "runs of at most 16 values");
   const int nwaves = blockDim.x / kWave;
   const int lane = __lane_id();
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int64_t w = (int64_t)blockIdx.x * nwaves + wv;
   const int64_t W = (int64_t)gridDim.x * nwaves;
-  const int64_t nseg = a.nseg;
-  const int64_t E = offset_at(a.offsets, nseg);
-  const int64_t chunk = std::max<int64_t>(64, (((E + W - 1) / W) + 63) & ~(int64_t)63);
+  const int64_t E = offset_at(a.offsets, a.nseg);
+  const int64_t chunk = std::max<int64_t>(kRunsMinChunk, (((E + W - 1) / W) + 63) & ~(int64_t)63);
   const int64_t lo = std::min(w * chunk, E);
   const int64_t hi = std::min(lo + chunk, E);
   const bool end_slice = E > 0 ? (lo < E && hi == E) : (w == 0);
@@ -501,248 +711,16 @@ __device__ static void seg_wave_runs_in(const SegArgs& a, const float* __restric
   // later store by the same lane replaces it.
   if constexpr (FIX == kFixRelaunch)
     if (lane == 0) a.carry_out[w] = SegCarry{-1, 0.0, 0};
-
-  int64_t s = first_segment(a, lo);
-  int64_t sa = 0, sb = 0;
-  bool have = seek_segment(a, s, hi, E, end_slice, sa, sb, lane == 0);
-  double C = 0.0;  // partial of segment s over [max(sa, lo), current position)
-
-  const int shift = (int)((reinterpret_cast<uintptr_t>(x) & 15) >> 2);
-  const v4f* xa = reinterpret_cast<const v4f*>(x - shift);
-  const int64_t vlo = (lo + shift) >> 2;
-  const int64_t vhi = (hi + shift + 3) >> 2;
-  constexpr int64_t T = kWave * IPT;
-  const int64_t ntiles = lo < hi ? (vhi - vlo + T - 1) / T : 0;
-
-  // Offsets ring in LDS: entry i mod kRing holds offsets[i] (INT64_MAX
-  // past nseg) for i in [fill - kRing, fill).  At the top of a tile, when
-  // every load has completed, the blocks of 64 entries loaded at the top of
-  // the previous tile are written, and up to three more are requested, as
-  // many as fit without overwriting entries from s + 1 on.  A (sub-)tile
-  // reads entries s + 1 .. s + 64, those that are in the ring.
-  auto off_entry = [&](int64_t i) -> int64_t { return i <= nseg ? a.offsets[i] : INT64_MAX; };
-  int64_t fill = 0;
-  int npend = 0;
-  int64_t pend0 = 0, pend1 = 0, pend2 = 0;
-  // (base + lane) mod kRing; base is wave-uniform and below 2^31 + 4 kRing
-  // (nseg < 2^31), so the modulo is a 32-bit one.
-  auto ring_pos = [&](int64_t base) {
-    const int h = (int)((unsigned)__builtin_amdgcn_readfirstlane((int)base) % (unsigned)kRing) + lane;
-    return h >= kRing ? h - kRing : h;
-  };
-  auto put = [&](int64_t v, int64_t base) { lds_put(ring, ring_pos(base), v); };
-  auto refill = [&]() {
-    if (npend > 0) put(pend0, fill);
-    if (npend > 1) put(pend1, fill + kWave);
-    if (npend > 2) put(pend2, fill + 2 * kWave);
-    fill += (int64_t)npend * kWave;
-    npend = 0;
-    if (fill - (s + 1) < kWave) {  // first tile, or after a long stretch walked piece by piece
-      fill = s + 1;
-      put(off_entry(fill + lane), fill);
-      put(off_entry(fill + kWave + lane), fill + kWave);
-      put(off_entry(fill + 2 * kWave + lane), fill + 2 * kWave);
-      fill += 3 * kWave;
-    }
-    npend = (int)std::min<int64_t>(3, (kRing - (fill - (s + 1))) / kWave);
-    if (npend > 0) pend0 = off_entry(fill + lane);
-    if (npend > 1) pend1 = off_entry(fill + kWave + lane);
-    if (npend > 2) pend2 = off_entry(fill + 2 * kWave + lane);
-  };
-  // Batches whose mean segment is short walk each tile in parts of fewer
-  // rows, so that a part holds fewer than 64 starts: halves under a mean of
-  // 32 values, quarters (4 loads per thread) under 12.
-  const int nparts = (IPT >= 4 && E < 12 * nseg) ? 4 : (IPT >= 2 && E < 32 * nseg) ? 2 : 1;
-
-  // Tiles arrive by direct-to-LDS loads, so no registers are held while a
-  // tile is in flight.  Load instruction u writes lane i's vector at tile
-  // position 64 u + i, and lane i fetches the tile vector that the run
-  // reads expect there (run_swz is its own inverse, and it permutes within
-  // groups of 16 vectors, so each instruction still reads 1 KB in one
-  // piece).  Positions past the slice's last vector fetch that vector
-  // again; the values they hold lie at or past hi and are masked out.
-  const int rows = IPT / nparts;  // rows per part
-  auto issue_rows = [&](int64_t t, int u0, int nrows) {
-    const int64_t vb = vlo + t * T;
-#pragma unroll
-    for (int u = u0; u < u0 + nrows; ++u) {
-      const int pos = u * kWave + lane;
-      const int64_t g = std::min<int64_t>(vb + (pos ^ ((pos >> 4) & (rows - 1))), vhi - 1);  // run_swz<rows>(pos)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xa + g),
-                                       (LdsPtr<void>)(tile + u * kWave), 16, 0,
-                                       NT ? kCpolNT : 0);
-    }
-  };
-
   int64_t own_fix = -1;
-  if (ntiles > 0) issue_rows(0, 0, IPT);
-  // The tiles walked in parts of RS rows: part q's values are
-  // [e0 + 256 RS q, e0 + 256 RS (q + 1)), and lane l holds their run
-  // [256 RS q + 4 RS l, + 4 RS) as xr[4 RS q .. 4 RS q + 4 RS).  The loop
-  // over the tiles is instantiated per part size, so that the registers
-  // one layout keeps across the loop are not added to another's.
-  auto walk = [&](auto rs_tag) {
-    constexpr int RS = decltype(rs_tag)::value;
-    constexpr int NP = IPT / RS;
-    constexpr int RL = 4 * RS;  // values per lane run
-    constexpr int64_t P = (int64_t)kWave * RL;
-    for (int64_t t = 0; t < ntiles; ++t) {
-      // Tile t is in LDS and every offsets load has completed here.
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      __builtin_amdgcn_s_waitcnt(0);
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      if (!have) break;  // the slice is finished, and no load is in flight
-      refill();
-      const int64_t e0 = 4 * (vlo + t * T) - shift;
-      const int64_t e1 = 4 * (vlo + (t + 1) * T) - shift;
-      float xr[4 * IPT];
-      // Reads part Q's runs.  Its rows then hold nothing else that is still
-      // to be read, so the same rows of the next tile go in flight: a part
-      // holds only its own runs in registers while it is walked.
-      auto take = [&](auto q_tag) {
-        constexpr int Q = decltype(q_tag)::value;
-#pragma unroll
-        for (int jj = 0; jj < RS; ++jj) {
-          const v4f y = tile[run_swz<RS>(Q * kWave * RS + lane * RS + jj)];
-          xr[Q * RL + 4 * jj] = y.x;
-          xr[Q * RL + 4 * jj + 1] = y.y;
-          xr[Q * RL + 4 * jj + 2] = y.z;
-          xr[Q * RL + 4 * jj + 3] = y.w;
-        }
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(kWaitLds);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        if (t + 1 < ntiles) issue_rows(t + 1, Q * RS, RS);
-      };
-
-      // Reduce-by-key walk over part Q (values [f0, f1)); returns false,
-      // having changed nothing, when the part needs the per-piece walk.
-      auto try_runs = [&](auto q_tag) -> bool {
-        constexpr int Q = decltype(q_tag)::value;
-        const int64_t f0 = e0 + (int64_t)kWave * RL * Q;
-        const int64_t f1 = f0 + (int64_t)kWave * RL;
-        // Entries s + 1 .. s + vis are in the ring; a view of fewer than 64
-        // must end past the part to show every start in it.
-        const int vis = (int)std::min<int64_t>(kWave, fill - (s + 1));
-        if (vis <= 0) return false;
-        // O: the start of segment s + 1 + lane
-        const int64_t O = lane < vis ? lds_get_i64_now(ring, ring_pos(s + 1)) : INT64_MAX;
-        const bool valid = O < std::min(f1, hi);
-        const int m = __popcll(__ballot(valid));  // the valid lanes are 0 .. m-1
-        if (m >= vis) return false;
-        const int rel = valid ? (int)(O - f0) : 0;
-        const int r = rel / RL;  // lane whose run holds start `lane`
-        const int rn = dpp_move<kWaveShl1, 0xF, 0xF>(r);  // lane + 1's run (lane 63: unused)
-        const bool clash = valid && lane + 1 < m && rn == r;
-        if (__ballot(clash) != 0) return false;
-        // Start k (lane k) tells lane r_k where it lies.
-        lds_put_u32_now(slot, lane, 0u);
-        if (valid) lds_put_u32_now(slot, r, ((unsigned)(lane + 1) << 16) | (unsigned)rel);
-        const unsigned word = lds_get_u32_now(slot, lane);
-        float xv[RL];
-#pragma unroll
-        for (int i = 0; i < RL; ++i) xv[i] = xr[Q * RL + i];
-        if (f0 < lo || f1 > hi) {  // values outside the slice are not its own
-          const int64_t p = f0 + (int64_t)RL * lane;
-#pragma unroll
-          for (int i = 0; i < RL; ++i) xv[i] = (p + i >= lo && p + i < hi) ? xv[i] : 0.0f;
-        }
-        const bool has = word != 0u;
-        const int b = has ? (int)(word & 0xFFFFu) - RL * lane : RL;  // the start's place in the run
-        // The run's head and tail in binary64: an fp32 value widens exactly,
-        // and each of the at most RL - 1 additions rounds once, at 2^-53.
-        double run = 0.0, head = 0.0;
-#pragma unroll
-        for (int i = 0; i < RL; ++i) {
-          if (i > 0) {
-            const bool at = i == b;
-            head = at ? run : head;
-            run = at ? 0.0 : run;
-          }
-          run += (double)xv[i];
-        }
-        double v = run;
-        int f = has ? 1 : 0;
-        wave_segscan(v, f);
-        if (!f) v = C + v;  // lanes 0 .. l hold no start: the open segment continues
-        const double left = dpp_move<kWaveShr1, 0xF, 0xF>(v);  // lane - 1's scan (lane 0: unused)
-        const double total = (lane == 0 ? C : left) + head;
-        const int k = (int)(word >> 16) - 1;
-        if (has && k > 0 && k < m) a.out[s + k] = total;  // segment s + k lies in the part
-        const double c_next = read_lane(v, kWave - 1);
-        if (m > 0) {
-          const int r0 = __builtin_amdgcn_readfirstlane(r);
-          const int64_t o0 = read_lane(O, 0);
-          finish_piece<FIX>(a, s, sa, o0, read_lane(total, r0), lo, hi, w, chunk, &own_fix);
-          sa = read_lane(O, m - 1);
-          sb = read_lane(O, m);
-          s += m;
-        }
-        C = c_next;
-        return true;
-      };
-
-      // Piece by piece, as in seg_wave_slices, over the tile's values from
-      // part Q0 on, with the open partial C: each lane adds its values of a
-      // piece (tile positions [ra, rb)) by compensated fp32 adds, then the
-      // wavefront combine.  Parts Q0 + 1 .. NP - 1 are read first.
-      auto pieces_from = [&](auto q_tag) {
-        constexpr int Q0 = decltype(q_tag)::value;
-        static_for<Q0 + 1, NP>(take);
-        auto relp = [&](int64_t e) { return (int)std::min(std::max(e - e0, (int64_t)0), 4 * T); };
-        auto piece_sum = [&](int ra, int rb) {
-          const unsigned wd = (unsigned)(rb - ra);
-          CompF32 acc = ModeF32Comp::zero();
-#pragma unroll
-          for (int q = Q0; q < NP; ++q) {
-            if (q * kWave * RL >= rb || (q + 1) * kWave * RL <= ra) continue;
-            const unsigned r = (unsigned)(q * kWave * RL + RL * lane - ra);
-#pragma unroll
-            for (int i = 0; i < RL; ++i) ModeF32Comp::add_elem(acc, r + i < wd ? xr[q * RL + i] : 0.0f);
-          }
-          return comp_to_double(wave_reduce_dpp<OpComp>(acc));
-        };
-        int64_t A = std::max(std::max(sa, lo), e0 + Q0 * P), B = std::min(sb, hi);
-        while (have && B <= e1) {
-          finish_piece<FIX>(a, s, sa, sb, C + piece_sum(relp(A), relp(B)), lo, hi, w, chunk, &own_fix);
-          C = 0.0;
-          ++s;
-          have = seek_segment(a, s, hi, E, end_slice, sa, sb, lane == 0);
-          A = std::max(sa, lo);
-          B = std::min(sb, hi);
-        }
-        if (have) C += piece_sum(relp(A), relp(B));
-      };
-
-      // Parts in order; the first part that cannot take the reduce-by-key
-      // walk, and the rest of the tile, go piece by piece.
-      static_for_while<0, NP>([&](auto q_tag) -> bool {
-        take(q_tag);
-        if (try_runs(q_tag)) return true;
-        pieces_from(q_tag);
-        return false;
-      });
-    }
-  };
-  if constexpr (IPT == 4) {
-    if (nparts == 4)
-      walk(std::integral_constant<int, 1>{});
-    else if (nparts == 2)
-      walk(std::integral_constant<int, 2>{});
+  if (lo < hi || end_slice) {
+    const LdsPtr<v4f> tile = lds_ptr(lds_all[wv].tile);
+    const LdsPtr<unsigned> mask = lds_ptr(lds_all[wv].mask);
+    if (MAX_ROWS >= 8 && chunk > 4096)
+      seg_walk_runs<MAX_ROWS, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
+    else if (MAX_ROWS >= 4 && chunk > 512)
+      seg_walk_runs<MAX_ROWS >= 4 ? 4 : 2, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
     else
-      walk(std::integral_constant<int, 4>{});
-  } else if constexpr (IPT == 2) {
-    if (nparts == 2)
-      walk(std::integral_constant<int, 1>{});
-    else
-      walk(std::integral_constant<int, 2>{});
-  } else {
-    walk(std::integral_constant<int, 1>{});
-  }
-  if (have) {  // the segment open at the slice's end ends at or after hi
-    finish_piece<FIX>(a, s, sa, sb, C, lo, hi, w, chunk, &own_fix);
-    ++s;
-    seek_segment(a, s, hi, E, end_slice, sa, sb, lane == 0);  // empty segments at E
+      seg_walk_runs<2, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
   }
   if constexpr (FIX == kFixBarrier) {
     grid_barrier_published(a.words, gridDim.x, a.bar_groups, a.spin_limit, gen);
@@ -754,12 +732,6 @@ __device__ static void seg_wave_runs_in(const SegArgs& a, const float* __restric
       if (lane == 0) a.out[own_fix] = v;
     }
   }
-}
-
-template <int IPT, bool NT, int FIX>
-__device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds* lds_all) {
-  RunLds& L = lds_all[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];
-  seg_wave_runs_in<IPT, NT, FIX>(a, a.x, lds_ptr(L.tile), lds_ptr(L.slot), lds_ptr(L.ring));
 }
 
 // Workgroup-granular slices (long segments: few streams, little per-piece
@@ -918,13 +890,18 @@ __device__ __forceinline__ void seg_workgroup_slices(const SegArgs& a, Workgroup
 // One form runs per launch, so the forms share the workgroup's LDS, which
 // is dynamic: the reduce-by-key form needs one RunLds per wavefront, so a
 // small workgroup does not reserve the space of a 512-thread one.
+template <int MAX_ROWS>
 union SegLds {
   WorkgroupLds wg;
-  RunLds runs[kSegMaxWG / kWave];
+  RunLds<MAX_ROWS> runs[kSegMaxWG / kWave];
 };
 
-size_t seg_lds_bytes(int wg) {
-  return std::max(sizeof(WorkgroupLds), (size_t)(wg / kWave) * sizeof(RunLds));
+size_t run_lds_bytes(int max_rows) {
+  return max_rows == 8 ? sizeof(RunLds<8>) : max_rows == 4 ? sizeof(RunLds<4>) : sizeof(RunLds<2>);
+}
+
+size_t seg_lds_bytes(int wg, int max_rows) {
+  return std::max(sizeof(WorkgroupLds), (size_t)(wg / kWave) * run_lds_bytes(max_rows));
 }
 
 // The form of a launch: forced, or from the batch's mean segment length
@@ -938,15 +915,16 @@ __device__ __forceinline__ int seg_form(const SegArgs& a) {
                                                  : kSegWavePieces;
 }
 
-template <int IPT, bool NT, int FIX>
+template <int IPT, bool NT, int FIX, bool WIDE>
 __global__ __launch_bounds__(kSegMaxWG) void k_segmented(SegArgs a) {
   extern __shared__ __align__(16) unsigned char seg_lds[];
-  SegLds& lds = *reinterpret_cast<SegLds*>(seg_lds);
+  constexpr int MAX_ROWS = runs_max_rows(IPT, WIDE);
+  SegLds<MAX_ROWS>& lds = *reinterpret_cast<SegLds<MAX_ROWS>*>(seg_lds);
   const int form = seg_form<IPT>(a);
   if (form == kSegWorkgroup) {
     seg_workgroup_slices<IPT, NT, FIX>(a, lds.wg);
   } else if (form == kSegWaveRuns) {
-    if constexpr (IPT <= 4) seg_wave_runs<IPT, NT, FIX>(a, lds.runs);
+    if constexpr (IPT <= 4) seg_wave_runs<MAX_ROWS, NT, FIX>(a, lds.runs);
   } else {
     seg_wave_slices<IPT, NT, FIX>(a);
   }
@@ -975,13 +953,15 @@ namespace {
 int ipt_index(int ipt) { return ipt == 1 ? 0 : ipt == 2 ? 1 : ipt == 4 ? 2 : ipt == 8 ? 3 : -1; }
 
 struct SegTable {
-  const void* k[3][2][4];  // SegFix, nontemporal, ipt index
+  const void* k[3][2][4][2];  // SegFix, nontemporal, ipt index, wide
   template <int F, bool NT>
   void fill() {
-    k[F][NT][0] = reinterpret_cast<const void*>(&k_segmented<1, NT, F>);
-    k[F][NT][1] = reinterpret_cast<const void*>(&k_segmented<2, NT, F>);
-    k[F][NT][2] = reinterpret_cast<const void*>(&k_segmented<4, NT, F>);
-    k[F][NT][3] = reinterpret_cast<const void*>(&k_segmented<8, NT, F>);
+    k[F][NT][0][0] = k[F][NT][0][1] = reinterpret_cast<const void*>(&k_segmented<1, NT, F, false>);
+    k[F][NT][1][0] = reinterpret_cast<const void*>(&k_segmented<2, NT, F, false>);
+    k[F][NT][1][1] = reinterpret_cast<const void*>(&k_segmented<2, NT, F, true>);
+    k[F][NT][2][0] = reinterpret_cast<const void*>(&k_segmented<4, NT, F, false>);
+    k[F][NT][2][1] = reinterpret_cast<const void*>(&k_segmented<4, NT, F, true>);
+    k[F][NT][3][0] = k[F][NT][3][1] = reinterpret_cast<const void*>(&k_segmented<8, NT, F, false>);
   }
   SegTable() {
     fill<kFixTicket, false>();
@@ -1020,13 +1000,31 @@ red_plan default_seg_plan(int64_t nseg, const DeviceInfo& dev) {
   return p;
 }
 
+namespace {
+// Workgroups of wg threads per CU of the (wide or other) grid-barrier kernel
+// with `ipt` loads per thread: asked once.
+int seg_per_cu(int ii, int wg, bool wide, int* per_cu) {
+  static std::atomic<int> known[4][kSegMaxWG / kWave + 1][2];  // 0: not asked yet
+  std::atomic<int>& c = known[ii][wg / kWave][wide ? 1 : 0];
+  int v = c.load(std::memory_order_relaxed);
+  if (v == 0) {
+    RED_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, seg_table().k[kFixBarrier][0][ii][wide ? 1 : 0], wg,
+                                                         seg_lds_bytes(wg, runs_max_rows(1 << ii, wide))));
+    c.store(v, std::memory_order_relaxed);
+  }
+  *per_cu = v;
+  return RED_OK;
+}
+}  // namespace
+
 int seg_max_coresident(int ipt, int wg, const DeviceInfo& dev, int* n_wg) {
   const int ii = ipt_index(ipt);
   if (ii < 0) return set_error(RED_EINVAL, "bad ipt %d", ipt);
-  int per_cu = 0;
-  RED_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, seg_table().k[kFixBarrier][0][ii], wg,
-                                                         seg_lds_bytes(wg)));
-  *n_wg = per_cu * dev.cus;
+  int narrow = 0, wide = 0;
+  int rc = seg_per_cu(ii, wg, false, &narrow);
+  if (!rc) rc = seg_per_cu(ii, wg, true, &wide);
+  if (rc) return rc;
+  *n_wg = std::max(narrow, wide) * dev.cus;
   return RED_OK;
 }
 
@@ -1052,6 +1050,13 @@ int seg_launch(const SegLaunch& sl, const float* x, const int64_t* offsets, int6
       return set_error(RED_EINVAL, "segmented persistent: grid %d exceeds %d co-resident workgroups",
                        grid, maxg);
   }
+  // The wide kernel if all of the grid is resident with it.  The rule is the
+  // same for the three fix-ups, so that they walk the same tiles and give the
+  // same bits.
+  int wide_per_cu = 0;
+  int wrc = seg_per_cu(ii, p.wg, true, &wide_per_cu);
+  if (wrc) return wrc;
+  const bool wide = grid <= wide_per_cu * dev.cus;
   SegArgs a;
   a.x = x;
   a.offsets = offsets;
@@ -1076,7 +1081,8 @@ int seg_launch(const SegLaunch& sl, const float* x, const int64_t* offsets, int6
   const bool nt = (p.flags & RED_FLAG_NONTEMPORAL) != 0;
   const bool coop = barrier && (p.flags & RED_FLAG_PLAIN_LAUNCH) == 0;
   const int slot = timer_begin(s);
-  int rc = launch(seg_table().k[fix][nt ? 1 : 0][ii], grid, p.wg, args, s, coop, seg_lds_bytes(p.wg));
+  int rc = launch(seg_table().k[fix][nt ? 1 : 0][ii][wide ? 1 : 0], grid, p.wg, args, s, coop,
+                  seg_lds_bytes(p.wg, runs_max_rows(p.ipt, wide)));
   if (rc == RED_OK && fix == kFixRelaunch) {
     // One wavefront per possible slice (the wavefront-slice count bounds the
     // workgroup-slice count).
