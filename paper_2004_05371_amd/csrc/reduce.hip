@@ -368,12 +368,13 @@ constexpr double kModelTBasicUs = 4.2;        // one-workgroup kernel, fixed cos
 constexpr double kModelTsyncUs = 0.8;         // extra fixed cost of the device-wide kernel
 constexpr double kModelThrBasicGBps = 100.0;  // one workgroup
 constexpr double kModelThrMoreGBps = 7000.0;  // whole device
-// Above this many bytes the two-kernel relaunch variant overtakes the
-// atomic ticket (its publication cost grows with the grid): measured
-// device times per call 7.7 against 8.0 us at 1 MiB, 9.1 against 8.1 us at
-// 2 MiB.
-constexpr int64_t kAtomicMaxBytes = 1LL << 20;
-
+// Up to this many bytes the atomic-ticket kernel: one launch to issue, not
+// two (4 us of host time per call against 6.5), and no slower on the device
+// (us per back-to-back call issued from C++, ticket against relaunch: 1 MB
+// 5.3 / 6.6, 4 MB 5.7 / 7.2, 10 MB 6.0 / 6.6, 34 MB 9.7 / 9.3).  Beyond, a call
+// takes longer than its two launches, and the ticket's tail (67 MB 13.8
+// against 13.4 us) is what differs.
+constexpr int64_t kAtomicMaxBytes = 32LL << 20;
 int64_t single_wg_switch_bytes() {
   const double tb = kModelThrBasicGBps * 1e3, tm = kModelThrMoreGBps * 1e3;  // bytes / us
   const double c_basic = kModelTBasicUs * tb;                                // Eq. 1
@@ -387,8 +388,11 @@ int64_t single_wg_switch_bytes() {
 
 // Default plan (measured on MI355X): below the model's switch point one
 // 1024-thread workgroup; up to kAtomicMaxBytes the atomic-ticket variant;
-// beyond, the relaunch variant with 256 threads x 4 loads of 16 bytes, two
-// workgroups per CU (32 KiB in flight per CU) and nontemporal loads.
+// beyond, the relaunch variant; both with 256 threads x 4 loads of 16 bytes,
+// two workgroups per CU (32 KiB in flight per CU).  The ticket variant reads
+// with ordinary loads, which the caches serve faster (10 MB 6.0 us against
+// 6.9 with the nontemporal hint), the relaunch variant with the hint (62 MB
+// 12.6 us against 12.8, 134 MB 22.7 against 24.3).
 red_plan default_plan(int dtype, int64_t n, const DeviceInfo& dev) {
   red_plan p;
   const int64_t bytes = n * (dtype == RED_I32 || dtype == RED_F32 ? 4 : 2);
@@ -402,6 +406,7 @@ red_plan default_plan(int dtype, int64_t n, const DeviceInfo& dev) {
     return p;
   }
   p.variant = bytes <= kAtomicMaxBytes ? RED_VARIANT_ATOMIC : RED_VARIANT_RELAUNCH;
+  if (p.variant == RED_VARIANT_ATOMIC) p.flags = 0;
   p.wg = 256;
   p.ipt = 4;
   p.grid = 2 * dev.cus;  // capped by the work at launch
