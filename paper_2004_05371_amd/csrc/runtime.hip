@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <list>
 #include <map>
 #include <mutex>
@@ -45,7 +46,13 @@ int hip_fail(hipError_t e, const char* what) {
 namespace {
 
 std::mutex g_mu;
-std::map<int, DeviceInfo> g_dev;
+std::map<int, DeviceInfo> g_dev;  // records stay until the process ends
+// The records of the first devices again, for calls after a device's first:
+// one query and no lock.
+constexpr int kFastDevices = 64;
+std::atomic<const DeviceInfo*> g_dev_known[kFastDevices];
+// Streams whose kernel timer is on.
+std::atomic<int> g_timers_on{0};
 std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
 
 // Plan table: (kind, dtype, acc, bucket) -> plan.  kind 0 = red_sum,
@@ -91,9 +98,7 @@ int capture_stream(int dev, hipStream_t* out) {
 }
 
 int bucket(int64_t n) {
-  int b = 0;
-  while (b < 63 && ((int64_t)1 << b) < n) ++b;
-  return b;  // ceil(log2 n)
+  return n <= 1 ? 0 : 64 - __builtin_clzll((unsigned long long)n - 1);  // ceil(log2 n)
 }
 
 }  // namespace
@@ -125,6 +130,12 @@ bool stream_capturing(hipStream_t s) {
 }
 
 int ensure_device(const DeviceInfo** info) {
+  int now = 0;
+  if (hipGetDevice(&now) == hipSuccess && now >= 0 && now < kFastDevices)
+    if (const DeviceInfo* d = g_dev_known[now].load(std::memory_order_acquire)) {
+      *info = d;
+      return RED_OK;
+    }
   int count = 0;
   if (hipGetDeviceCount(&count) != hipSuccess || count < 1) {
     (void)hipGetLastError();
@@ -161,6 +172,7 @@ int ensure_device(const DeviceInfo** info) {
   d.nxcc = nx;
   auto r = g_dev.emplace(dev, d);
   *info = &r.first->second;
+  if (dev < kFastDevices) g_dev_known[dev].store(*info, std::memory_order_release);
   return RED_OK;
 }
 
@@ -229,6 +241,7 @@ namespace {
 // while the timer is on), or -1; with `record`, its start event is
 // recorded on the stream now.
 int timer_acquire(hipStream_t s, bool record, hipEvent_t* start = nullptr, hipEvent_t* stop = nullptr) {
+  if (g_timers_on.load(std::memory_order_relaxed) == 0) return -1;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return -1;
   std::lock_guard<std::mutex> lk(g_mu);
@@ -500,6 +513,7 @@ void red_shutdown(void) {
     }
   }
   g_timers.clear();
+  g_timers_on = 0;
   for (auto& kv : g_ws) {
     (void)hipSetDevice(kv.first.first);
     (void)hipFree(kv.second.base);
@@ -1009,6 +1023,7 @@ int red_kernel_timer(void* stream, int enable) {
   std::lock_guard<std::mutex> lk(g_mu);
   if (enable < 0) return set_error(RED_EINVAL, "enable must be >= 0");
   KernelTimer& t = g_timers[std::make_pair(dev->id, s)];
+  g_timers_on += (enable > 0) - (t.period > 0);
   t.period = enable;
   t.launches = 0;
   t.used = 0;
