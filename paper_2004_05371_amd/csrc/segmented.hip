@@ -14,10 +14,10 @@
 //     the current one is added into fp32 TwoSum-compensated accumulators,
 //     or, in the reduce-by-key form, into binary64 per-lane runs);
 //   * the segments are finished in one of three forms, chosen on the device
-//     from the mean segment length: a piece that ends in a tile is finished
+//     from the mean segment length and a sample of lengths: a piece that ends in a tile is finished
 //     by a wavefront combine per wave, completed in batches of 64 pieces
 //     after one workgroup barrier (workgroup slices); by one DPP wavefront
-//     combine (wavefront slices); or, for very short segments, the wavefront
+//     combine (wavefront slices); or, for short or ragged ones, the wavefront
 //     reduces by key over per-lane runs of consecutive values with a
 //     segmented scan across its lanes (seg_wave_runs);
 //   * a segment that lies inside the slice is written directly (binary64);
@@ -56,8 +56,11 @@ struct SegArgs {
   unsigned spin_limit;
   unsigned bar_groups;
   int form;  // SegForm: automatic, or one form forced
-  int grid;  // workgroups of the slice kernel
-  int wg;    // threads per workgroup of the slice kernel
+  // Workgroups of the slice kernel and threads per workgroup.  The kernels
+  // take the sizes from here: blockDim.x costs a dependent load through
+  // vector memory, 0.2 to 0.4 us per call where a wavefront has little to do.
+  int grid;
+  int wg;
 };
 
 // How the pieces of a segment cut by slice boundaries are summed.
@@ -69,7 +72,7 @@ enum SegFix : int {
 
 // How the slices are cut and walked.
 enum SegForm : int {
-  kSegAuto = 0,        // chosen on the device from the mean segment length
+  kSegAuto = 0,        // chosen on the device (seg_form)
   kSegWorkgroup = 1,   // workgroup slices
   kSegWavePieces = 2,  // wavefront slices, one combine per piece
   kSegWaveRuns = 3,    // wavefront slices, reduce-by-key over lane runs
@@ -243,19 +246,22 @@ struct PieceInfo {
 constexpr int kSegMaxWG = 512;
 
 // Batches whose mean segment holds fewer values than this take wavefront
-// slices, the others workgroup slices (measured on MI355X: 64- to
+// slices, the others workgroup slices, where seg_form does not choose the
+// reduce-by-key form (measured on MI355X: 64- to
 // 4096-value segments run 2 to 8 times faster on wavefront slices, long
 // ones about 10 to 30 % faster on workgroup slices).
 constexpr int64_t kWaveSliceMeanLen = 16384;
 
-// Batches whose mean segment holds fewer values than this take the
-// reduce-by-key form of the wavefront slices (plans of at most 4 loads per
-// thread).  Measured on MI355X with 60 M values, 256 x 4, four workgroups
-// per CU, us per call against one combine per piece: equal segments of 512
-// values 52.7 against 62.0, of 1024 49.8 against 48.5; of random length
-// (mean 512) 52.4 against 72.8, (mean 1024) 50.1 against 53.8, (mean 2048)
-// 49.0 against 47.5.
+// Batches whose mean segment holds fewer values than kRunsMeanLen always
+// take the reduce-by-key form (plans of at most 4 loads per thread), ragged
+// ones up to kRunsRaggedLen.  us per call against one combine per piece, 60 M
+// values: equal segments of 512 values 50.2 against 62.0, of 1024 47.5
+// against 48.2, of 2048 46.3 against 44.9; of random length (mean 512) 50.2
+// against 72.8, (mean 1024) 48.0 against 53.8, (mean 4096) 46.3 against 45.2.
+// Log-uniform lengths of mean 65536 take the same in both (10 M values 18.5
+// us), since there the pieces of one segment count on one ticket.
 constexpr int64_t kRunsMeanLen = 1024;
+constexpr int64_t kRunsRaggedLen = 65536;
 
 // Wavefront-granular slices (short segments: every wave walks its own
 // pieces, with no workgroup barrier): wavefront w of the grid owns slice
@@ -265,10 +271,10 @@ __device__ __forceinline__ void seg_wave_slices(const SegArgs& a) {
   // Barrier fix-up: thread 0 holds the barrier generation of this launch.
   unsigned gen = FIX == kFixBarrier ? grid_barrier_gen(a.words) : 0u;
   using M = ModeF32Comp;
-  const int nwaves = blockDim.x / kWave;
+  const int nwaves = a.wg / kWave;
   const int lane = __lane_id();
   const int64_t w = (int64_t)blockIdx.x * nwaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int64_t W = (int64_t)gridDim.x * nwaves;
+  const int64_t W = (int64_t)a.grid * nwaves;
   const int64_t nseg = a.nseg;
   const int64_t E = offset_at(a.offsets, nseg);
   const int64_t chunk = std::max<int64_t>(64, (((E + W - 1) / W) + 63) & ~(int64_t)63);
@@ -353,7 +359,7 @@ __device__ __forceinline__ void seg_wave_slices(const SegArgs& a) {
     for (int u = 0; u < IPT; ++u) cur[u] = nxt[u];
   }
   if constexpr (FIX == kFixBarrier) {
-    grid_barrier_published(a.words, gridDim.x, a.bar_groups, a.spin_limit, gen);
+    grid_barrier_published(a.words, a.grid, a.bar_groups, a.spin_limit, gen);
     if (own_fix >= 0) {
       __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the pieces are loaded as published
       const int64_t o = offset_at(a.offsets, own_fix) / chunk;
@@ -680,30 +686,37 @@ __device__ __forceinline__ void seg_walk_runs(const SegArgs& a, const LdsPtr<v4f
 
 // Slices of at least this many values: below, more wavefronts do not shorten
 // a call, and shorter slices cut more segments (1 M values in segments of
-// about 200: 8.4 us per call against 10.0 with slices down to 64).
+// about 200: 8.4 us per call against 10.0 with slices down to 64).  Long
+// segments take slices of a sixteenth of the mean segment, up to
+// kRunsLongChunk, so that not too many pieces of one count on one ticket, 60
+// ns each (1 M values in 15 log-uniform segments: 10.7 us against 18.9).
 constexpr int64_t kRunsMinChunk = 512;
+constexpr int64_t kRunsLongChunk = 4096;
 
 // Rows of the largest tile.  The wide kernels keep 16 wavefronts per CU (125
 // VGPRs with 8 rows), the others 20 and more; the host takes a wide one for a
 // grid that is then wholly resident.
 constexpr int runs_max_rows(int ipt, bool wide) { return ipt == 4 ? (wide ? 8 : 4) : ipt == 2 && wide ? 4 : 2; }
 
-// Tiles of 8 rows (2048 values) for slices of more than 4096 values, so that
-// a tile's fixed work is spread over more values (64 M values in segments of
-// 64: 56 us against 63 with 4 rows); 4 rows below, so that a short slice is
-// still two tiles or more and one loads while the other is walked (8 M
-// values: 15.6 us against 16.9 with 8 rows); 2 rows for slices of 512.
+// Tiles of 8 rows (2048 values) for slices of more than 7168 values (three
+// and a half such tiles), so that a tile's fixed work is spread over more values (32 M
+// values in segments of 64: 31.0 us against 32.8 with 4 rows); 4 rows below,
+// so that a short slice is still several tiles, the last of them nearly
+// full, and one loads while the other is walked (20 M values: 21.5 us against
+// 23.8 with 8 rows); 2 rows for slices of 512.
 template <int MAX_ROWS, bool NT, int FIX>
 __device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds<MAX_ROWS>* lds_all) {
   // Barrier fix-up: thread 0 holds the barrier generation of this launch.
   unsigned gen = FIX == kFixBarrier ? grid_barrier_gen(a.words) : 0u;
-  const int nwaves = blockDim.x / kWave;
+  const int nwaves = a.wg / kWave;
   const int lane = __lane_id();
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int64_t w = (int64_t)blockIdx.x * nwaves + wv;
-  const int64_t W = (int64_t)gridDim.x * nwaves;
+  const int64_t W = (int64_t)a.grid * nwaves;
   const int64_t E = offset_at(a.offsets, a.nseg);
-  const int64_t chunk = std::max<int64_t>(kRunsMinChunk, (((E + W - 1) / W) + 63) & ~(int64_t)63);
+  const int64_t mean = (int64_t)((float)E / (float)a.nseg);
+  const int64_t chunk = std::max<int64_t>({kRunsMinChunk, (((E + W - 1) / W) + 63) & ~(int64_t)63,
+                                           std::min<int64_t>(mean / 16, kRunsLongChunk) & ~(int64_t)63});
   const int64_t lo = std::min(w * chunk, E);
   const int64_t hi = std::min(lo + chunk, E);
   const bool end_slice = E > 0 ? (lo < E && hi == E) : (w == 0);
@@ -715,7 +728,7 @@ __device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds<MAX_ROWS>
   if (lo < hi || end_slice) {
     const LdsPtr<v4f> tile = lds_ptr(lds_all[wv].tile);
     const LdsPtr<unsigned> mask = lds_ptr(lds_all[wv].mask);
-    if (MAX_ROWS >= 8 && chunk > 4096)
+    if (MAX_ROWS >= 8 && chunk > 7168)
       seg_walk_runs<MAX_ROWS, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
     else if (MAX_ROWS >= 4 && chunk > 512)
       seg_walk_runs<MAX_ROWS >= 4 ? 4 : 2, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
@@ -723,7 +736,7 @@ __device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds<MAX_ROWS>
       seg_walk_runs<2, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
   }
   if constexpr (FIX == kFixBarrier) {
-    grid_barrier_published(a.words, gridDim.x, a.bar_groups, a.spin_limit, gen);
+    grid_barrier_published(a.words, a.grid, a.bar_groups, a.spin_limit, gen);
     if (own_fix >= 0) {
       __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the pieces are loaded as published
       const int64_t o = offset_at(a.offsets, own_fix) / chunk;
@@ -760,7 +773,7 @@ __device__ __forceinline__ void seg_workgroup_slices(const SegArgs& a, Workgroup
   int buf = 0, nb = 0;
   const int64_t nseg = a.nseg;
   const int64_t E = offset_at(a.offsets, nseg);
-  const int64_t G = gridDim.x;
+  const int64_t G = a.grid;
   const int64_t g = blockIdx.x;
   const int64_t chunk = std::max<int64_t>(64, (((E + G - 1) / G) + 63) & ~(int64_t)63);
   const int64_t lo = std::min(g * chunk, E);
@@ -783,7 +796,7 @@ __device__ __forceinline__ void seg_workgroup_slices(const SegArgs& a, Workgroup
   const v4f* xa = reinterpret_cast<const v4f*>(a.x - shift);
   const int64_t vlo = (lo + shift) >> 2;
   const int64_t vhi = (hi + shift + 3) >> 2;  // vectors [vlo, vhi) hold the slice
-  const int64_t bs = blockDim.x;
+  const int64_t bs = a.wg;
   const int64_t T = bs * IPT;
   const int64_t ntiles = lo < hi ? (vhi - vlo + T - 1) / T : 0;
   const int tid = threadIdx.x;
@@ -875,7 +888,7 @@ __device__ __forceinline__ void seg_workgroup_slices(const SegArgs& a, Workgroup
   }
   if (nb > 0) flush();
   if constexpr (FIX == kFixBarrier) {
-    grid_barrier_published(a.words, gridDim.x, a.bar_groups, a.spin_limit, gen);  // also a workgroup barrier
+    grid_barrier_published(a.words, a.grid, a.bar_groups, a.spin_limit, gen);  // also a workgroup barrier
     const int64_t os = own_fix;
     if (os >= 0 && wave == 0) {
       __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the pieces are loaded as published
@@ -904,15 +917,33 @@ size_t seg_lds_bytes(int wg, int max_rows) {
   return std::max(sizeof(WorkgroupLds), (size_t)(wg / kWave) * run_lds_bytes(max_rows));
 }
 
-// The form of a launch: forced, or from the batch's mean segment length
-// (the same decision in every workgroup, and in the fix-up kernel).
+// The form of a launch: forced, or from the batch's mean segment length and,
+// for plans of at most 4 loads per thread, from the lengths of 64 segments
+// evenly spaced over the batch (the same decision in every workgroup).  The
+// reduce-by-key form takes what is short, what leaves a thread less than one
+// value, and what is ragged, which the other forms walk one segment after
+// another: up to a mean of 65536 if half of the sample is shorter than a
+// quarter of the mean, up to 2048 if one segment of it is twice the mean.  us
+// per call, the other form / reduce-by-key: 10 M values, log-uniform lengths
+// of mean 1024 27.5 / 16.5, 4096 19.8 / 15.4, 32768 20.3 / 15.4; random cuts
+// of mean 1024 19.0 / 17.0, 2048 16.8 / 17.0; equal lengths of 4096 13.7 /
+// 14.7, 32768 12.6 / 14.0; 100,000 values, equal lengths of 65536 16.7 / 7.9.
+// The sample costs the other forms 0.4 us (1 M values, equal lengths of
+// 4096: 8.4 us without it, 8.8 with).
 template <int IPT>
 __device__ __forceinline__ int seg_form(const SegArgs& a) {
   if (a.form != kSegAuto) return a.form;
+  const v2l sample = *reinterpret_cast<const v2l*>(a.offsets + (((int64_t)__lane_id() * a.nseg) >> 6));
   const int64_t E = offset_at(a.offsets, a.nseg);
-  return E >= kWaveSliceMeanLen * a.nseg ? kSegWorkgroup
-         : (IPT <= 4 && E < kRunsMeanLen * a.nseg) ? kSegWaveRuns
-                                                 : kSegWavePieces;
+  if constexpr (IPT <= 4) {
+    if (E < kRunsMeanLen * a.nseg || E < (int64_t)a.grid * a.wg) return kSegWaveRuns;
+    if (E < kRunsRaggedLen * a.nseg) {
+      const float len = (float)(sample.y - sample.x) * (float)a.nseg;
+      if (__popcll(__ballot(4.0f * len < (float)E)) >= kWave / 2) return kSegWaveRuns;
+      if (E < 2 * kRunsMeanLen * a.nseg && __ballot(len >= 2.0f * (float)E) != 0) return kSegWaveRuns;
+    }
+  }
+  return E >= kWaveSliceMeanLen * a.nseg ? kSegWorkgroup : kSegWavePieces;
 }
 
 template <int IPT, bool NT, int FIX, bool WIDE>

@@ -452,3 +452,29 @@ def test_persistent_batch_replays_from_a_graph(lib):
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy(), want), i
     assert lib.red_check_error(s) == lib.RED_OK
+
+
+@pytest.mark.parametrize("variant", [1, 2, 3])
+@pytest.mark.parametrize("mean", [1000, 1500, 3000, 20000, 70000])
+def test_ragged_and_even_batches_of_one_mean(lib, mean, variant):
+    """The automatic form is chosen from the mean length and a sample of 64
+    lengths: batches below, between and above its lines, of equal lengths,
+    random cuts, half short and a few long ones, and all values in one
+    segment of the sample; fewer and more than 64 segments; the three
+    fix-ups with 2 and 4 loads."""
+    rng = np.random.default_rng(mean)
+    for nseg in (5, 64, 200):
+        E = mean * nseg + 17
+        cuts = np.sort(rng.integers(0, E + 1, nseg - 1))
+        w = np.exp(rng.random(nseg) * np.log(1 << 20))
+        skew = np.minimum((np.cumsum(w)[:-1] * (E / w.sum())).astype(np.int64), E)
+        one = np.where(np.arange(1, nseg) > nseg // 2, E - nseg, 0) + np.arange(1, nseg)
+        even = np.arange(1, nseg) * mean
+        for k, mid in enumerate((cuts, skew, one, even)):
+            off = np.concatenate([[0], mid, [E]]).astype(np.int64)
+            x = inputs.mixed_f32(E, sub=200 + k)
+            for ipt in (2, 4):
+                g = min(64, lib.red_max_coresident_segmented(ipt, 256))
+                flags = lib.FLAG_PLAIN_LAUNCH if variant == 3 else 0
+                check(run(lib, x, off, variant=variant, wg=256, ipt=ipt, grid=g, flags=flags), x, off)
+            check(run(lib, x, off), x, off)
