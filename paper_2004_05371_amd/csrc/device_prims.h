@@ -238,16 +238,15 @@ __device__ __forceinline__ typename Op::T wave_reduce_bpermute(typename Op::T v)
 
 // ---------------------------------------------------------------------------
 // Workgroup combine: per-wave totals -> LDS -> s_barrier -> wave 0 combines.
-// Returns the workgroup total in every lane of wave 0 (other waves get
+// Returns the workgroup total of its nwaves in every lane of wave 0 (others get
 // zero()).  `lds` holds at least kMaxWavesPerWG values.  The caller must
 // place a __syncthreads() before reusing `lds`.
 // ---------------------------------------------------------------------------
 template <class Op>
-__device__ __forceinline__ typename Op::T block_reduce(typename Op::T v, typename Op::T* lds) {
+__device__ __forceinline__ typename Op::T block_reduce(typename Op::T v, typename Op::T* lds, int nwaves) {
   using T = typename Op::T;
   const int wave = threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
-  const int nwaves = blockDim.x / kWave;
   T w = wave_reduce_dpp<Op>(v);
   if (lane == 0) lds[wave] = w;
   __syncthreads();
