@@ -33,6 +33,7 @@
 
 #include "device_prims.h"
 #include "internal.h"
+#include "stencil_plan.h"
 
 namespace redsum {
 
@@ -295,8 +296,6 @@ __device__ __forceinline__ void window_steps(float (&x)[V], int steps, float r, 
     loop(std::false_type{}, std::true_type{});
 }
 
-constexpr int kTileWG = 256;  // four wavefronts, one per SIMD; they do not cooperate
-
 // Lane l's V values from p + V l on, by the widest loads that the array's
 // alignment (4 bytes) and V allow.
 typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -409,113 +408,35 @@ int stencil_coresident(int vpt, int wg, const DeviceInfo& dev, int* n_wg) {
   return RED_OK;
 }
 
-// Shapes of the blocked-step form: windows of 64 V values.
-struct TileKernel {
-  int v;
-  const void* fn;
-};
-const TileKernel kTileKernels[] = {
-    {2, reinterpret_cast<const void*>(&k_jacobi_tile<2>)},   {4, reinterpret_cast<const void*>(&k_jacobi_tile<4>)},
-    {6, reinterpret_cast<const void*>(&k_jacobi_tile<6>)},   {8, reinterpret_cast<const void*>(&k_jacobi_tile<8>)},
-    {12, reinterpret_cast<const void*>(&k_jacobi_tile<12>)}, {16, reinterpret_cast<const void*>(&k_jacobi_tile<16>)},
-    {20, reinterpret_cast<const void*>(&k_jacobi_tile<20>)}, {24, reinterpret_cast<const void*>(&k_jacobi_tile<24>)},
-    {28, reinterpret_cast<const void*>(&k_jacobi_tile<28>)}, {36, reinterpret_cast<const void*>(&k_jacobi_tile<36>)},
-};
-
-// One wavefront for the whole array: up to 64 x 8 interior values.
-struct OneWindowKernel {
-  int v;
-  double us_per_step;  // measured
-  const void* fn;
-};
-const OneWindowKernel kOneWindowKernels[] = {
-    {2, 0.044, reinterpret_cast<const void*>(&k_jacobi_one_window<2>)},
-    {4, 0.064, reinterpret_cast<const void*>(&k_jacobi_one_window<4>)},
-    {8, 0.104, reinterpret_cast<const void*>(&k_jacobi_one_window<8>)},
-};
-
-struct TilePlan {
-  const void* fn = nullptr;
-  int launches = 0;  // 1: the one-window kernel; else even, u and scratch alternating
-  int k = 0;         // window margin: at least the steps of one launch
-  int m = 0;         // interior values that a window advances
-  int64_t waves = 0;
-};
-
-// Cost of a launch besides its steps: the kernel boundary, the ramp and the
-// first load (2.2 us from 1 K to 64 K values), and the array's read and
-// write.  While every wavefront is resident at once all of them load before
-// they compute (about 10 TB/s beyond the 2.2 us, from the caches); beyond
-// that the loads run under other wavefronts' steps at a large copy's rate,
-// 4.8 TB/s (24 M values, 4 steps: 40 us), less for runs longer than 64 bytes
-// per lane, whose loads and stores touch more lines at a time.
-constexpr double kTileLaunchUs = 2.2;
-constexpr double kTileCachedBytesPerUs = 10e6;
-constexpr double kTileStreamBytesPerUs = 4.8e6;
-
-// Cycles per VALU operation and SIMD with w wavefronts resident on it
-// (measured: 4 M and 1 M values with windows of 12 to 36 values per lane).
-double tile_cycles_per_op(double w) { return w <= 1 ? 4.6 : w <= 2 ? 3.2 : w <= 3 ? 2.9 : 2.75; }
-
-// The shape of the lowest modelled time for N interior values and `steps`
-// steps.  More steps per launch save launches and widen the recomputed
-// margins; a larger window has relatively narrower margins, but a small
-// array then leaves SIMDs idle, and a step takes as long as the fullest SIMD
-// (4 V operations per wavefront on it).
-TilePlan plan_tiles(int64_t N, int steps, const DeviceInfo& dev) {
-  TilePlan best;
-  double best_us = 1e300;
-  if (N <= 8 * kWave)
-    for (const OneWindowKernel& k : kOneWindowKernels)
-      if (N <= (int64_t)k.v * kWave) {
-        best.fn = k.fn;
-        best.launches = 1;
-        best_us = kTileLaunchUs + k.us_per_step * steps;
-        break;
-      }
-  const double cyc_us = dev.clock_khz * 1e-3;
-  for (const TileKernel& t : kTileKernels) {
-    const int w_vals = kWave * t.v;
-    if (N < w_vals) break;
-    // From the fewest launches whose margins leave a quarter of the window,
-    // up in steps of about a third, eight candidates.
-    int64_t L = std::max<int64_t>(2, (steps + 24 * t.v - 1) / (24 * t.v));
-    for (int c = 0; c < 8; ++c) {
-      L += L & 1;
-      const int per = (int)((steps + L - 1) / L);
-      const int k = (per + 3) & ~3;  // keeps the block edges of interior windows on whole vectors
-      const int m = w_vals - 2 * k;
-      const int64_t waves = (N + m - 1) / m;
-      const int64_t wgs = (waves + kTileWG / kWave - 1) / (kTileWG / kWave);
-      const bool resident = wgs <= 8 * (int64_t)dev.cus;
-      const double load = resident ? (double)((wgs + dev.cus - 1) / dev.cus) : (double)wgs / dev.cus + 0.5;
-      const double step_us = per * load * (4 * t.v + 2) * tile_cycles_per_op(load) / cyc_us;
-      double us;
-      if (resident) {
-        us = step_us + 8.0 * (double)N / kTileCachedBytesPerUs;
-      } else {
-        const double mem_us = 8.0 * (double)N / kTileStreamBytesPerUs * (t.v <= 16 ? 1.0 : t.v <= 20 ? 1.15 : 1.35);
-        us = std::max(step_us, mem_us) + 0.2 * std::min(step_us, mem_us);
-      }
-      us = (double)L * (us + kTileLaunchUs);
-      if (us < best_us) {
-        best_us = us;
-        best = TilePlan{t.fn, (int)L, k, m, waves};
-      }
-      if (per <= 8) break;
-      L += std::max<int64_t>(2, L / 3);
-    }
+// Kernels of the blocked-step shapes that plan_tiles() chooses from.
+const void* tile_kernel(int v) {
+  switch (v) {
+    case 2: return reinterpret_cast<const void*>(&k_jacobi_tile<2>);
+    case 4: return reinterpret_cast<const void*>(&k_jacobi_tile<4>);
+    case 6: return reinterpret_cast<const void*>(&k_jacobi_tile<6>);
+    case 8: return reinterpret_cast<const void*>(&k_jacobi_tile<8>);
+    case 12: return reinterpret_cast<const void*>(&k_jacobi_tile<12>);
+    case 16: return reinterpret_cast<const void*>(&k_jacobi_tile<16>);
+    case 20: return reinterpret_cast<const void*>(&k_jacobi_tile<20>);
+    case 24: return reinterpret_cast<const void*>(&k_jacobi_tile<24>);
+    case 28: return reinterpret_cast<const void*>(&k_jacobi_tile<28>);
+    default: return reinterpret_cast<const void*>(&k_jacobi_tile<36>);
   }
-  return best;
+}
+
+const void* one_window_kernel(int v) {
+  return v == 2   ? reinterpret_cast<const void*>(&k_jacobi_one_window<2>)
+         : v == 4 ? reinterpret_cast<const void*>(&k_jacobi_one_window<4>)
+                  : reinterpret_cast<const void*>(&k_jacobi_one_window<8>);
 }
 
 int tile_launch(float* u, float* scratch, int64_t n, int steps, float r, hipStream_t s, const DeviceInfo& dev) {
   int64_t N = n - 2;
-  TilePlan t = plan_tiles(N, steps, dev);
+  TilePlan t = plan_tiles(N, steps, dev.cus, dev.clock_khz);
   if (t.launches == 1) {
     int n32 = (int)N;
     void* args[] = {&u, &n32, &steps, &r};
-    return launch(t.fn, 1, kWave, args, s, false);
+    return launch(one_window_kernel(t.v), 1, kWave, args, s, false);
   }
   const int grid = (int)((t.waves + kTileWG / kWave - 1) / (kTileWG / kWave));
   float* src = u;
@@ -523,7 +444,7 @@ int tile_launch(float* u, float* scratch, int64_t n, int steps, float r, hipStre
   for (int64_t i = 0; i < t.launches; ++i) {
     int now = (int)(steps * (i + 1) / t.launches - steps * i / t.launches);
     void* args[] = {&src, &dst, &N, &t.m, &t.k, &now, &r};
-    int rc = launch(t.fn, grid, kTileWG, args, s, false);
+    int rc = launch(tile_kernel(t.v), grid, kTileWG, args, s, false);
     if (rc) return rc;
     std::swap(src, dst);
   }
