@@ -332,7 +332,9 @@ int red_sum_segmented_loop(const float *x, const int64_t *host_offsets, int64_t 
  *                                    neighbouring windows recompute, u and
  *                                    scratch alternating over an even
  *                                    number of ordinary launches (one, in
- *                                    place, up to 514 values); any length.
+ *                                    place, for up to 514 values and few
+ *                                    steps); any length.  One or two steps
+ *                                    on 2 M values and more: as RELAUNCH.
  *                                    steps_per_sync and the launch flags
  *                                    below concern the persistent form and
  *                                    are not used here.  With plan.wg or

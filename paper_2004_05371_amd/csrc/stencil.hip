@@ -430,9 +430,8 @@ const void* one_window_kernel(int v) {
                   : reinterpret_cast<const void*>(&k_jacobi_one_window<8>);
 }
 
-int tile_launch(float* u, float* scratch, int64_t n, int steps, float r, hipStream_t s, const DeviceInfo& dev) {
-  int64_t N = n - 2;
-  TilePlan t = plan_tiles(N, steps, dev.cus, dev.clock_khz);
+// `steps` steps of N = n - 2 interior values in the shape t (t.launches > 0).
+int tile_launch(TilePlan t, float* u, float* scratch, int64_t N, int steps, float r, hipStream_t s) {
   if (t.launches == 1) {
     int n32 = (int)N;
     void* args[] = {&u, &n32, &steps, &r};
@@ -458,15 +457,21 @@ int stencil_launch(float* u, float* scratch, int64_t n, int steps, float r, int 
   if (n < 3 || steps == 0) return RED_OK;
   int variant = p.variant;
   // AUTO without a workgroup size or grid of the caller's (which are shapes
-  // of the other forms): blocked steps.  At every size they were faster than
-  // both (1000 steps on 64 K values: 70 us against 200 for the persistent
-  // form; 200 steps on 4 M: 84 against 188; 40 steps on 24 M, which only
-  // one launch per step could run: 93 against 1220).
+  // of the other forms): blocked steps, or one launch per step where that is
+  // faster (stencil_plan.h).  From three steps on, blocked steps were faster
+  // than both other forms at every size (1000 steps on 64 K values: 65 us
+  // against 200 for the persistent form; 200 steps on 4 M: 77 against 188;
+  // 40 steps on 24 M, which only one launch per step could run: 92 against
+  // 1250).
   if (variant == RED_VARIANT_AUTO && p.wg == 0 && p.grid == 0) {
-    const int slot = timer_begin(s);
-    const int rc = tile_launch(u, scratch, n, steps, r, s, dev);
-    timer_end(s, slot);
-    return rc;
+    const TilePlan t = plan_tiles(n - 2, steps, dev.cus, dev.clock_khz);
+    if (t.launches > 0) {
+      const int slot = timer_begin(s);
+      const int rc = tile_launch(t, u, scratch, n - 2, steps, r, s);
+      timer_end(s, slot);
+      return rc;
+    }
+    variant = RED_VARIANT_RELAUNCH;
   }
   // The geometry (workgroups, block length) is set for the caller's halo,
   // or for a halo of 8 when the library chooses it.

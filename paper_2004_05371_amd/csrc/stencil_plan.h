@@ -25,7 +25,7 @@ constexpr OneWindow kOneWindows[] = {{2, 0.044}, {4, 0.064}, {8, 0.104}};
 
 struct TilePlan {
   int v = 0;         // values per lane
-  int launches = 0;  // 1: the one-window kernel; else even, u and scratch alternating
+  int launches = 0;  // 0: one launch per step instead; 1: the one-window kernel; else even, u and scratch alternating
   int k = 0;         // window margin: at least the steps of one launch
   int m = 0;         // interior values that a window advances
   int64_t waves = 0;
@@ -46,6 +46,16 @@ constexpr double kTileStreamBytesPerUs = 4.8e6;
 // (measured: 4 M and 1 M values with windows of 12 to 36 values per lane).
 inline double tile_cycles_per_op(double w) { return w <= 1 ? 4.6 : w <= 2 ? 3.2 : w <= 3 ? 2.9 : 2.75; }
 
+// One or two steps on this many values and more run as one launch per step:
+// two passes over the array either way, and whole-array streams pass at 6.5
+// TB/s where windows pass at 4.8 (one step, us as launches per step / as
+// windows: 1 M values 6.4 / 6.1, 2 M 7.5 / 8.5, 4 M 11.9 / 16.7, 16 M 40 /
+// 68, 24 M 58 / 79, 100 M 320 / 355; two steps 6.4 / 6.1, 8.4 / 8.6, 12.6 /
+// 16.7, 42 / 67, 60 / 79, 334 / 353).  Three steps are four passes against
+// two (4 M 24.4 / 16.6, 24 M 119 / 80).
+constexpr int kStepLaunchMaxSteps = 2;
+constexpr int64_t kStepLaunchMinValues = 2 << 20;
+
 // The shape of the lowest modelled time for N interior values and `steps`
 // steps.  More steps per launch save launches and widen the recomputed
 // margins; a larger window has relatively narrower margins, but a small
@@ -53,6 +63,7 @@ inline double tile_cycles_per_op(double w) { return w <= 1 ? 4.6 : w <= 2 ? 3.2 
 // (4 V operations per wavefront on it).
 inline TilePlan plan_tiles(int64_t N, int steps, int cus, int64_t clock_khz) {
   TilePlan best;
+  if (steps <= kStepLaunchMaxSteps && N >= kStepLaunchMinValues) return best;
   double best_us = 1e300;
   if (N <= 8 * kTileLanes)
     for (const OneWindow& k : kOneWindows)

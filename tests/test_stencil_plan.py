@@ -38,6 +38,9 @@ def test_shapes_cover_the_array(plan, n):
     cases = [(n, s) for s in (1, 2, 3, 8, 40, 200, 863, 864, 1000, 12_345, 10**6, INT_MAX - 864, INT_MAX - 863,
                               INT_MAX - 47, INT_MAX)]
     for (_, steps), (v, launches, k, m, waves) in zip(cases, plan(cases)):
+        if launches == 0:  # one launch per step
+            assert steps <= 2 and n >= 2**21, (n, steps)
+            continue
         if launches == 1:
             assert v in (2, 4, 8) and n <= 64 * v, (n, steps, v)
             continue
@@ -47,3 +50,12 @@ def test_shapes_cover_the_array(plan, n):
         assert m >= 1 and m == 64 * v - 2 * k, (n, steps, k, m)
         assert waves == -(-n // m), (n, steps, m, waves)
         assert -(-waves // 4) * 256 < 2**32, (n, steps, waves)
+
+
+def test_one_launch_per_step_where_it_is_faster(plan):
+    """One or two steps on 2^21 interior values and more; three steps, or
+    fewer values, run on windows."""
+    for n, steps, per_step in ((2**21 - 1, 1, False), (2**21, 1, True), (2**21, 2, True), (2**21, 3, False),
+                               (10_000_000, 1, True), (24_000_001, 2, True), (24_000_001, 3, False), (4096, 1, False)):
+        (_, launches, _, _, _), = plan([(n, steps)])
+        assert (launches == 0) == per_step, (n, steps, launches)
