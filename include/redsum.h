@@ -221,7 +221,9 @@ int red_sum_ex(int dtype, const void *x, int64_t n, void *out, void *stream, con
 /* red_sum_ex that allocates nothing, for callers that cannot allocate device
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments, plans, kernels and results as
- * red_sum_ex (the same plan gives the same bits).
+ * red_sum_ex (the same plan gives the same bits), but for the default plan:
+ * where red_sum's is the atomic ticket this one runs its shape as two kernels,
+ * which need no cleared words (the same bits).
  *   Scratch: the partials and barrier words live in one static device
  *   array of the library (80 KiB of words + RED_NOALLOC_MAX_GRID x 8 bytes,
  *   held by every device the library runs on until the process ends), not

@@ -93,6 +93,9 @@ struct ReduceLaunch {
   red_plan plan;  // plan.flags: RED_FLAG_NONTEMPORAL | RED_FLAG_PLAIN_LAUNCH
   bool timed = true;             // may carry the stream's kernel-timer events
   int max_grid = RED_MAX_GRID;   // partial slots the workspace holds
+  // Relaunch variant: the final combine in the order of the one-kernel
+  // variants (one 256-thread workgroup), for the same bits as theirs.
+  bool final_workgroup = false;
 };
 int validate_plan(const red_plan& p);
 red_plan default_plan(int dtype, int64_t n, const DeviceInfo& dev);

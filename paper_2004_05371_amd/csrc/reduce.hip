@@ -483,7 +483,7 @@ int reduce_launch(const ReduceLaunch& rl, const void* x, int64_t n, void* out, W
       if (rc) return rc;
       // Up to 1024 partials: one wavefront (at most 16 loads per lane);
       // beyond: one 256-thread workgroup.
-      const bool wave = grid <= 1024;
+      const bool wave = grid <= 1024 && !rl.final_workgroup;
       void* part = ws->partials;
       void* fargs[] = {&part, &grid, &out};
       const void* fn = is_int ? (wave ? reinterpret_cast<const void*>(&k_final_wave<long long>)

@@ -416,12 +416,14 @@ red_plan complete_plan(red_plan p, const red_plan& dflt) {
   return p;
 }
 
-red_plan lookup_plan(int dtype, int acc, int64_t n, const DeviceInfo& dev) {
+// The installed plan, else the default (*is_default, if asked for).
+red_plan lookup_plan(int dtype, int acc, int64_t n, const DeviceInfo& dev, bool* is_default = nullptr) {
   {
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_plans.find(std::make_tuple(0, dtype, dtype == RED_I32 ? 0 : acc, bucket(n)));
     if (it != g_plans.end()) return it->second;
   }
+  if (is_default) *is_default = true;
   return default_plan(dtype, n, dev);
 }
 
@@ -593,11 +595,22 @@ int red_sum_noalloc(int dtype, const void* x, int64_t n, void* out, void* stream
   ws.words = reinterpret_cast<BarrierWords*>(sp);
   ws.partials = static_cast<char*>(sp) + kWordsBytes;
   ReduceLaunch rl;
+  bool is_default = false;
   rl.dtype = dtype;
   rl.acc = opts ? opts->acc : RED_ACC_COMPENSATED;
   rl.plan = (opts && opts->plan.variant != RED_VARIANT_AUTO)
                 ? complete_plan(opts->plan, default_plan(dtype, n, *dev))
-                : lookup_plan(dtype, rl.acc, n, *dev);
+                : lookup_plan(dtype, rl.acc, n, *dev, &is_default);
+  // The default plan's ticket saves a launch, but not here, where a clear of
+  // the ticket lines goes before it: two kernels without one are faster from
+  // 0.5 MB up (us per call, ticket / relaunch: 2 MB 6.1 / 5.8, 8 MB 6.9 / 6.1,
+  // 31 MB 8.2 / 6.2 from the caches; 2 MB 6.5 / 5.9, 8 MB 7.7 / 6.3, 31 MB
+  // 11.1 / 9.0 from HBM).  The combine in the ticket's order, so that the
+  // bits stay those of red_sum.
+  if (is_default && rl.plan.variant == RED_VARIANT_ATOMIC) {
+    rl.plan.variant = RED_VARIANT_RELAUNCH;
+    rl.final_workgroup = true;
+  }
   if (opts) rl.plan.flags |= opts->flags & (RED_FLAG_NONTEMPORAL | RED_FLAG_PLAIN_LAUNCH | RED_FLAG_PIPELINE | RED_FLAG_XCD);
   rl.timed = false;
   rl.max_grid = RED_NOALLOC_MAX_GRID;
