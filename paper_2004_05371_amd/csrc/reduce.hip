@@ -375,12 +375,15 @@ constexpr double kModelTsyncUs = 0.8;         // extra fixed cost of the device-
 constexpr double kModelThrBasicGBps = 100.0;  // one workgroup
 constexpr double kModelThrMoreGBps = 7000.0;  // whole device
 // Up to this many bytes the atomic-ticket kernel: one launch to issue, not
-// two (4 us of host time per call against 6.5), and no slower on the device
-// (us per back-to-back call issued from C++, ticket against relaunch: 1 MB
-// 5.3 / 6.6, 4 MB 5.7 / 7.2, 10 MB 6.0 / 6.6, 34 MB 9.7 / 9.3).  Beyond, a call
-// takes longer than its two launches, and the ticket's tail (67 MB 13.8
-// against 13.4 us) is what differs.
+// two (us per call from Python, where issuing takes longest, ticket / relaunch:
+// 16 MB 6.0 / 8.6, 28 MB 6.7 / 8.6 from the caches, 7.4 / 8.4 and 9.1 / 8.7
+// from HBM).  On the device it is faster up to 6 MB; above, its tail costs up
+// to 6 % of a stream of calls that the host issues faster than that (from C++:
+// 4 MB 4.8 / 5.9, 16 MB 5.9 / 6.0, 28 MB 6.6 / 6.1 from the caches; 4 MB 5.3 /
+// 6.0, 8 MB 6.2 / 6.0, 16 MB 7.3 / 6.9, 28 MB 9.0 / 8.6 from HBM).  Beyond the
+// line a call takes longer than its two launches either way.
 constexpr int64_t kAtomicMaxBytes = 32LL << 20;
+
 int64_t single_wg_switch_bytes() {
   const double tb = kModelThrBasicGBps * 1e3, tm = kModelThrMoreGBps * 1e3;  // bytes / us
   const double c_basic = kModelTBasicUs * tb;                                // Eq. 1
@@ -395,10 +398,10 @@ int64_t single_wg_switch_bytes() {
 // Default plan (measured on MI355X): below the model's switch point one
 // 1024-thread workgroup; up to kAtomicMaxBytes the atomic-ticket variant;
 // beyond, the relaunch variant; both with 256 threads x 4 loads of 16 bytes,
-// two workgroups per CU (32 KiB in flight per CU).  The ticket variant reads
-// with ordinary loads, which the caches serve faster (10 MB 6.0 us against
-// 6.9 with the nontemporal hint), the relaunch variant with the hint (62 MB
-// 12.6 us against 12.8, 134 MB 22.7 against 24.3).
+// two workgroups per CU (32 KiB in flight per CU) and nontemporal loads, which
+// cost nothing where the caches hold the input (ticket, ordinary / hinted: 10
+// MB 5.62 / 5.60 us) and save 1 to 2 % where they do not (16 MB 7.42 / 7.27;
+// relaunch, 134 MB 24.3 / 22.7).
 red_plan default_plan(int dtype, int64_t n, const DeviceInfo& dev) {
   red_plan p;
   const int64_t bytes = n * (dtype == RED_I32 || dtype == RED_F32 ? 4 : 2);
@@ -412,7 +415,6 @@ red_plan default_plan(int dtype, int64_t n, const DeviceInfo& dev) {
     return p;
   }
   p.variant = bytes <= kAtomicMaxBytes ? RED_VARIANT_ATOMIC : RED_VARIANT_RELAUNCH;
-  if (p.variant == RED_VARIANT_ATOMIC) p.flags = 0;
   p.wg = 256;
   p.ipt = 4;
   p.grid = 2 * dev.cus;  // capped by the work at launch
