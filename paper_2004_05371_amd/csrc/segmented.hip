@@ -41,6 +41,7 @@
 
 #include "device_prims.h"
 #include "internal.h"
+#include "seg_rules.h"
 
 namespace redsum {
 
@@ -68,14 +69,6 @@ enum SegFix : int {
   kFixTicket = 0,    // the wavefront that publishes the last piece (atomic ticket)
   kFixBarrier = 1,   // the owning slice, after a grid barrier (co-resident grid)
   kFixRelaunch = 2,  // a second kernel, after the implicit barrier between launches
-};
-
-// How the slices are cut and walked.
-enum SegForm : int {
-  kSegAuto = 0,        // chosen on the device (seg_form)
-  kSegWorkgroup = 1,   // workgroup slices
-  kSegWavePieces = 2,  // wavefront slices, one combine per piece
-  kSegWaveRuns = 3,    // wavefront slices, reduce-by-key over lane runs
 };
 
 // offsets[i] through the scalar data cache (the offsets are read-only for
@@ -244,24 +237,6 @@ struct PieceInfo {
 // 16-byte vectors and IPT compensated accumulators in registers, which for
 // IPT = 8 needs more than the 128 VGPRs a 1024-thread workgroup allows.
 constexpr int kSegMaxWG = 512;
-
-// Batches whose mean segment holds fewer values than this take wavefront
-// slices, the others workgroup slices, where seg_form does not choose the
-// reduce-by-key form (measured on MI355X: 64- to
-// 4096-value segments run 2 to 8 times faster on wavefront slices, long
-// ones about 10 to 30 % faster on workgroup slices).
-constexpr int64_t kWaveSliceMeanLen = 16384;
-
-// Batches whose mean segment holds fewer values than kRunsMeanLen always
-// take the reduce-by-key form (plans of at most 4 loads per thread), ragged
-// ones up to kRunsRaggedLen.  us per call against one combine per piece, 60 M
-// values: equal segments of 512 values 50.2 against 62.0, of 1024 47.5
-// against 48.2, of 2048 46.3 against 44.9; of random length (mean 512) 50.2
-// against 72.8, (mean 1024) 48.0 against 53.8, (mean 4096) 46.3 against 45.2.
-// Log-uniform lengths of mean 65536 take the same in both (10 M values 18.5
-// us), since there the pieces of one segment count on one ticket.
-constexpr int64_t kRunsMeanLen = 1024;
-constexpr int64_t kRunsRaggedLen = 65536;
 
 // Wavefront-granular slices (short segments: every wave walks its own
 // pieces, with no workgroup barrier): wavefront w of the grid owns slice
@@ -919,31 +894,27 @@ size_t seg_lds_bytes(int wg, int max_rows) {
 
 // The form of a launch: forced, or from the batch's mean segment length and,
 // for plans of at most 4 loads per thread, from the lengths of 64 segments
-// evenly spaced over the batch (the same decision in every workgroup).  The
-// reduce-by-key form takes what is short, what leaves a thread less than one
-// value, and what is ragged, which the other forms walk one segment after
-// another: up to a mean of 65536 if half of the sample is shorter than a
-// quarter of the mean, up to 2048 if one segment of it is twice the mean.  us
-// per call, the other form / reduce-by-key: 10 M values, log-uniform lengths
-// of mean 1024 27.5 / 16.5, 4096 19.8 / 15.4, 32768 20.3 / 15.4; random cuts
-// of mean 1024 19.0 / 17.0, 2048 16.8 / 17.0; equal lengths of 4096 13.7 /
-// 14.7, 32768 12.6 / 14.0; 100,000 values, equal lengths of 65536 16.7 / 7.9.
-// The sample costs the other forms 0.4 us (1 M values, equal lengths of
-// 4096: 8.4 us without it, 8.8 with).
+// evenly spaced over the batch (the same decision in every workgroup; the
+// rules and their figures are in seg_rules.h).  The sample costs the forms
+// that it does not change 0.4 us (1 M values, equal lengths of 4096: 8.4 us
+// without it, 8.8 with).
 template <int IPT>
 __device__ __forceinline__ int seg_form(const SegArgs& a) {
   if (a.form != kSegAuto) return a.form;
   const v2l sample = *reinterpret_cast<const v2l*>(a.offsets + (((int64_t)__lane_id() * a.nseg) >> 6));
   const int64_t E = offset_at(a.offsets, a.nseg);
   if constexpr (IPT <= 4) {
-    if (E < kRunsMeanLen * a.nseg || E < (int64_t)a.grid * a.wg) return kSegWaveRuns;
+    if (short_batch(E, a.nseg, (int64_t)a.grid * a.wg)) return kSegWaveRuns;
     if (E < kRunsRaggedLen * a.nseg) {
-      const float len = (float)(sample.y - sample.x) * (float)a.nseg;
-      if (__popcll(__ballot(4.0f * len < (float)E)) >= kWave / 2) return kSegWaveRuns;
-      if (E < 2 * kRunsMeanLen * a.nseg && __ballot(len >= 2.0f * (float)E) != 0) return kSegWaveRuns;
+      const long long next = dpp_move<kWaveShl1, 0xF, 0xF>((long long)sample.x);
+      const SampledSegment l = sampled_segment(E, a.nseg, sample.x, sample.y, next);
+      auto lanes = [](bool p) { return (int)__popcll(__ballot(p)); };
+      const SegSample c{lanes(l.is_short), lanes(l.is_short && l.is_filled), lanes(l.is_filled), lanes(l.is_joined),
+                        lanes(l.is_long)};
+      if (ragged_batch(E, a.nseg, c)) return kSegWaveRuns;
     }
   }
-  return E >= kWaveSliceMeanLen * a.nseg ? kSegWorkgroup : kSegWavePieces;
+  return long_form(E, a.nseg);
 }
 
 template <int IPT, bool NT, int FIX, bool WIDE>
