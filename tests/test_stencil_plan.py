@@ -16,6 +16,11 @@ pytestmark = pytest.mark.skipif(CXX is None, reason="needs g++")
 
 INT_MAX = 2**31 - 1
 
+# Values per lane -> (n, steps) of an array that the planner gives windows of
+# that width; the GPU tests run these.
+WIDTHS = {2: (1000, 50), 4: (65_536, 131), 6: (100_003, 200), 8: (262_146, 131), 12: (1_000_002, 200),
+          16: (1_890_062, 60), 20: (4_194_304, 200), 24: (2_965_823, 75), 28: (5_163_796, 84), 36: (8_684_434, 117)}
+
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
@@ -59,3 +64,9 @@ def test_one_launch_per_step_where_it_is_faster(plan):
                                (10_000_000, 1, True), (24_000_001, 2, True), (24_000_001, 3, False), (4096, 1, False)):
         (_, launches, _, _, _), = plan([(n, steps)])
         assert (launches == 0) == per_step, (n, steps, launches)
+
+
+def test_every_window_width_has_a_size(plan):
+    """The sizes that stand for the widths in the GPU tests take them."""
+    got = plan([(n - 2, steps) for n, steps in WIDTHS.values()])
+    assert [g[0] for g in got] == list(WIDTHS) and all(g[1] >= 2 for g in got), got
