@@ -1,9 +1,11 @@
-// How a segmented batch is walked (k_segmented in segmented.hip): the
-// arithmetic of the choice, with no HIP call in it, so that a test without a
-// GPU evaluates what the kernel evaluates.
+// How a segmented batch is walked and how its slices are cut (k_segmented in
+// segmented.hip): the arithmetic of the choices, with no HIP call in it, so
+// that a test without a GPU evaluates what the kernel evaluates.
 #pragma once
 
 #include <stdint.h>
+
+#include <algorithm>
 
 #ifdef __HIP__
 #define RED_HD __host__ __device__ __forceinline__
@@ -103,5 +105,50 @@ RED_HD bool ragged_batch(int64_t E, int64_t nseg, const SegSample& c) {
   if (c.n_joined >= 16 && (nseg >= 1024 || (nseg >= 512 && c.n_filled >= 8))) return true;
   return E < kWaveSliceMeanLen * nseg ? E < kSpreadEmptyMaxValues : nseg <= 64 && c.n_filled < 32;
 }
+
+// Slices of at least this many values: below, more wavefronts do not shorten
+// a call, and shorter slices cut more segments (1 M values in segments of
+// about 200: 8.4 us per call against 10.0 with slices down to 64).  Long
+// segments take slices of a sixteenth of the mean segment, up to
+// kRunsLongChunk, so that not too many pieces of one count on one ticket (1 M
+// values in 15 log-uniform segments: 10.7 us against 18.9).
+constexpr int64_t kRunsMinChunk = 512;
+constexpr int64_t kRunsLongChunk = 4096;
+
+// Values of a slice of the reduce-by-key form over W wavefronts.
+RED_HD int64_t runs_slice(int64_t E, int64_t nseg, int64_t W) {
+  const int64_t mean = (int64_t)((float)E / (float)nseg);
+  return std::max<int64_t>({kRunsMinChunk, (((E + W - 1) / W) + 63) & ~(int64_t)63,
+                            std::min<int64_t>(mean / 16, kRunsLongChunk) & ~(int64_t)63});
+}
+
+// Rows of the largest tile.  The wide kernels keep 16 wavefronts per CU (125
+// VGPRs with 8 rows), the others 20 and more; the host takes a wide one for a
+// grid that is then wholly resident.
+constexpr int runs_max_rows(int ipt, bool wide) { return ipt == 4 ? (wide ? 8 : 4) : ipt == 2 && wide ? 4 : 2; }
+
+// Rows (64 vectors of 4 values) of the tiles that a slice is walked in: 8
+// (2048 values) for slices of more than 7168 values (three and a half such
+// tiles), so that a tile's fixed work is spread over more values (32 M values
+// in segments of 64: 31.0 us against 32.8 with 4 rows); 4 rows below, so that a
+// short slice is still several tiles, the last of them nearly full, and one
+// loads while the other is walked (20 M values: 21.5 us against 23.8 with 8
+// rows); 2 rows for slices of 512.
+constexpr int64_t kRows8Above = 7168, kRows4Above = 512;
+RED_HD int runs_rows(int max_rows, int64_t slice) {
+  return max_rows >= 8 && slice > kRows8Above ? 8 : max_rows >= 4 && slice > kRows4Above ? 4 : 2;
+}
+
+// Vectors of a tile buffer, and the place in it of the tile's vector i: one
+// vector of padding after every 8, so that the run reads (lane l, vector
+// ROWS l + j) of neighbouring lanes fall in distinct banks, as do the writes of
+// a row, and every read and write of a lane lies at a fixed distance from its
+// first.
+constexpr int run_tile_vectors(int rows) { return 64 * rows * 9 / 8; }
+RED_HD constexpr int run_place(int i) { return i + (i >> 3); }
+
+// A tile with more non-empty segments than this holds more sums than its LDS
+// has room for, and is walked in halves.
+constexpr int run_max_starts(int rows) { return 2 * 64 * rows; }
 
 }  // namespace redsum

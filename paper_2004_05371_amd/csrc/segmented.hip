@@ -381,8 +381,8 @@ __device__ __forceinline__ void seg_wave_slices(const SegArgs& a) {
 // of 4 114 / 2864, 16 66 / 72, 64 56 / 61, 512 52 / 57.
 template <int ROWS>
 struct RunLds {
-  v4f tile[kWave * ROWS * 9 / 8];  // one tile of up to ROWS rows, padded; then sums by rank
-  unsigned mask[kWave];            // per lane run: bit i set when a segment starts at its value i
+  v4f tile[run_tile_vectors(ROWS)];  // one tile of up to ROWS rows, padded; then sums by rank
+  unsigned mask[kWave];              // per lane run: bit i set when a segment starts at its value i
 };
 
 constexpr int kChunks = 4;  // chunks of 64 offsets loaded a tile ahead
@@ -402,12 +402,6 @@ __device__ __forceinline__ void wave_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
-
-// Place in the tile buffer of the tile's vector i: one vector of padding
-// after every 8, so that the run reads (lane l, vector ROWS l + j) of
-// neighbouring lanes fall in distinct banks, as do the writes of a row, and
-// every read and write of a lane lies at a fixed distance from its first.
-__device__ __forceinline__ constexpr int run_place(int i) { return i + (i >> 3); }
 
 // Lanes of the ballot b below the calling one.
 __device__ __forceinline__ int lanes_below(uint64_t b) {
@@ -535,7 +529,7 @@ __device__ __forceinline__ void seg_walk_runs(const SegArgs& a, const LdsPtr<v4f
     mask[lane] = 0u;
     wave_order();
     if constexpr (RL == 4 * ROWS)
-      if (R > 2 * kWave * ROWS) return false;
+      if (R > run_max_starts(ROWS)) return false;
     const int q0 = q;
     q += cnt;
     load_entries();
@@ -659,26 +653,8 @@ __device__ __forceinline__ void seg_walk_runs(const SegArgs& a, const LdsPtr<v4f
     for (int64_t i = (int64_t)q + lane; i < nseg; i += kWave) a.out[i] = 0.0;
 }
 
-// Slices of at least this many values: below, more wavefronts do not shorten
-// a call, and shorter slices cut more segments (1 M values in segments of
-// about 200: 8.4 us per call against 10.0 with slices down to 64).  Long
-// segments take slices of a sixteenth of the mean segment, up to
-// kRunsLongChunk, so that not too many pieces of one count on one ticket, 60
-// ns each (1 M values in 15 log-uniform segments: 10.7 us against 18.9).
-constexpr int64_t kRunsMinChunk = 512;
-constexpr int64_t kRunsLongChunk = 4096;
-
-// Rows of the largest tile.  The wide kernels keep 16 wavefronts per CU (125
-// VGPRs with 8 rows), the others 20 and more; the host takes a wide one for a
-// grid that is then wholly resident.
-constexpr int runs_max_rows(int ipt, bool wide) { return ipt == 4 ? (wide ? 8 : 4) : ipt == 2 && wide ? 4 : 2; }
-
-// Tiles of 8 rows (2048 values) for slices of more than 7168 values (three
-// and a half such tiles), so that a tile's fixed work is spread over more values (32 M
-// values in segments of 64: 31.0 us against 32.8 with 4 rows); 4 rows below,
-// so that a short slice is still several tiles, the last of them nearly
-// full, and one loads while the other is walked (20 M values: 21.5 us against
-// 23.8 with 8 rows); 2 rows for slices of 512.
+// The reduce-by-key form over the slices of runs_slice() values, in tiles of
+// runs_rows() rows.
 template <int MAX_ROWS, bool NT, int FIX>
 __device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds<MAX_ROWS>* lds_all) {
   // Barrier fix-up: thread 0 holds the barrier generation of this launch.
@@ -689,9 +665,7 @@ __device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds<MAX_ROWS>
   const int64_t w = (int64_t)blockIdx.x * nwaves + wv;
   const int64_t W = (int64_t)a.grid * nwaves;
   const int64_t E = offset_at(a.offsets, a.nseg);
-  const int64_t mean = (int64_t)((float)E / (float)a.nseg);
-  const int64_t chunk = std::max<int64_t>({kRunsMinChunk, (((E + W - 1) / W) + 63) & ~(int64_t)63,
-                                           std::min<int64_t>(mean / 16, kRunsLongChunk) & ~(int64_t)63});
+  const int64_t chunk = runs_slice(E, a.nseg, W);
   const int64_t lo = std::min(w * chunk, E);
   const int64_t hi = std::min(lo + chunk, E);
   const bool end_slice = E > 0 ? (lo < E && hi == E) : (w == 0);
@@ -703,9 +677,9 @@ __device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds<MAX_ROWS>
   if (lo < hi || end_slice) {
     const LdsPtr<v4f> tile = lds_ptr(lds_all[wv].tile);
     const LdsPtr<unsigned> mask = lds_ptr(lds_all[wv].mask);
-    if (MAX_ROWS >= 8 && chunk > 7168)
+    if (MAX_ROWS >= 8 && chunk > kRows8Above)  // runs_rows(), with no value to keep
       seg_walk_runs<MAX_ROWS, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
-    else if (MAX_ROWS >= 4 && chunk > 512)
+    else if (MAX_ROWS >= 4 && chunk > kRows4Above)
       seg_walk_runs<MAX_ROWS >= 4 ? 4 : 2, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
     else
       seg_walk_runs<2, NT, FIX>(a, tile, mask, w, chunk, lo, hi, E, end_slice, own_fix);
