@@ -253,9 +253,9 @@ int red_sum_noalloc(int dtype, const void *x, int64_t n, void *out, void *stream
  *   out     device pointer to nseg doubles.  Empty segments give 0.
  * A fixed grid: every workgroup (long segments) or every wavefront (short
  * ones) owns an equal slice of the elements and sums the pieces of the
- * segments that meet its slice; for very short segments a wavefront
- * reduces by key over runs of consecutive values with a segmented scan
- * across its lanes.  The pieces of segments that cross slice boundaries
+ * segments that meet its slice; for short segments, and for ragged batches
+ * up to a mean of 65536 values, a wavefront reduces by key over runs of
+ * consecutive values with a segmented scan across its lanes.  The pieces of segments that cross slice boundaries
  * are combined in slice order in binary64, by default by the wavefront
  * that publishes a segment's last piece, found with an atomic ticket
  * (red_sum_segmented_ex lists the other ways).  The kernels are

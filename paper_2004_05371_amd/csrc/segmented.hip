@@ -14,12 +14,13 @@
 //     the current one is added into fp32 TwoSum-compensated accumulators,
 //     or, in the reduce-by-key form, into binary64 per-lane runs);
 //   * the segments are finished in one of three forms, chosen on the device
-//     from the mean segment length and a sample of lengths: a piece that ends in a tile is finished
-//     by a wavefront combine per wave, completed in batches of 64 pieces
-//     after one workgroup barrier (workgroup slices); by one DPP wavefront
-//     combine (wavefront slices); or, for short or ragged ones, the wavefront
-//     reduces by key over per-lane runs of consecutive values with a
-//     segmented scan across its lanes (seg_wave_runs);
+//     from the mean segment length and a sample of lengths (seg_rules.h): a
+//     piece that ends in a tile is finished by a wavefront combine per wave,
+//     completed in batches of 64 pieces after one workgroup barrier (workgroup
+//     slices); by one DPP wavefront combine (wavefront slices); or, for short
+//     or ragged ones, the wavefront reduces by key over per-lane runs of
+//     consecutive values with a segmented scan across its lanes
+//     (seg_wave_runs);
 //   * a segment that lies inside the slice is written directly (binary64);
 //     a piece of a segment that crosses a slice boundary goes to a carry
 //     slot, and the pieces of that segment are summed in slice order in
@@ -370,10 +371,15 @@ __device__ __forceinline__ void seg_wave_slices(const SegArgs& a) {
 // no scan.  A tile with more starts than its LDS holds sums (half its
 // values) is walked in two halves, which cannot.
 //
-// What bounds it below about 64 values per segment is instruction issue: per
-// row of 64 values about 10 operations, and about 250 per tile, which is
-// why the runs are as long as four wavefronts per SIMD have registers for;
-// above, the reading of the values.  The walk it replaced finished every
+// What bounds it is latency that four wavefronts per SIMD do not hide: the
+// steps of a tile depend on one another through LDS and memory.  By the
+// counters a wavefront waits for one of these 48 % of its time (32 M values in
+// segments of 16 on average) or 42 % (67 M in segments of 512), for its turn to
+// issue 26 and 31 %; the VALU is busy about a quarter of the time, LDS 23 and
+// 29 %, 9 and 0.4 % of that with bank conflicts.  So the runs are as long as
+// four wavefronts have registers for, to spread a tile's fixed steps, about 250
+// operations, over more values (about 10 operations per row of 64; smaller
+// tiles with five or six wavefronts were slower).  The walk it replaced finished every
 // tile with an empty segment, or with two starts in one run, piece by piece,
 // bound by the chain of dependent steps of each piece.  64 M values, us per
 // call now and before: segments of random length (empty ones among them) of

@@ -2,7 +2,9 @@
 // (seg_wave_runs in paper_2004_05371_amd/csrc/segmented.hip): mask words per
 // lane run, sums by rank in the tile's own LDS, chunks of 64 offsets, half
 // tiles where a tile holds more starts than sums fit.  Test infrastructure only: nothing of the
-// library is linked or included.
+// library is linked or included.  Its slices and rows are its own (slices down
+// to 64 values, 2 ipt rows); seg_slices_emu.cpp runs whole launches with those
+// of the kernel.
 //
 // Per-lane values are arrays of 64.  Checked: every global access (value
 // vectors that overlap the batch, offsets[0 .. nseg], out[0 .. nseg)), every

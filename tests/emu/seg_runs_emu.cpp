@@ -1,6 +1,8 @@
-// Lane-level CPU emulation of the reduce-by-key form of the segmented batch
-// (seg_wave_runs in paper_2004_05371_amd/csrc/segmented.hip) and of the
-// relaunch fix-up kernel (k_seg_fixup), with a bounds check on every access.
+// Lane-level CPU emulation of a former reduce-by-key form of the segmented
+// batch (parts of a tile, an offsets ring) and of the relaunch fix-up kernel
+// (k_seg_fixup), with a bounds check on every access.  The library has another
+// walk now: seg_slices_emu.cpp emulates that one.  "The kernel" below is the
+// former one.
 //
 // Test infrastructure only: nothing of the library is linked or included.
 // The emulation restates the kernel's steps for one wavefront at a time,

@@ -95,7 +95,8 @@ def test_binomial_impulse(lib):
 def test_large_persistent_and_auto_fallback(lib):
     """A million values for 200 steps in one persistent launch; an array
     larger than the co-resident windows is refused by the persistent
-    form and run by one launch per step under AUTO."""
+    form and run under AUTO (by blocked steps; AUTO with a shape, which
+    falls back to one launch per step, is in test_gpu_stencil_auto.py)."""
     x = inputs.normal_f32((1 << 20) + 5, sub=63)
     want = oracle.jacobi_1d_f32(x, 200, 0.4)
     for spsync in (1, 16):

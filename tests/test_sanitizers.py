@@ -10,7 +10,7 @@ CPU:
   with no GPU present.
 
 (The lane-level emulation of the segmented kernel runs under the same
-sanitizers in test_seg_runs_emulation.py.)"""
+sanitizers in test_seg_slices_emulation.py.)"""
 import os
 import shutil
 import subprocess

@@ -1,12 +1,13 @@
-"""Lane-level CPU emulation of the segmented batch's reduce-by-key form
-(seg_wave_runs) and relaunch fix-up (k_seg_fixup), tests/emu/seg_runs_emu.cpp:
-every global, LDS and cross-lane access bounds-checked, the kernel's own
-invariants checked, every segment's sum compared exactly (integer values).
+"""Lane-level CPU emulation of a former reduce-by-key form of the segmented
+batch (the library has another walk now, see test_seg_slices_emulation.py) and
+of the relaunch fix-up (k_seg_fixup), tests/emu/seg_runs_emu.cpp: every global,
+LDS and cross-lane access bounds-checked, the kernel's own invariants checked,
+every segment's sum compared exactly (integer values).
 
 Covered geometries include the one of a GPU memory fault seen while two
 changes to this form were under test: 2^28 values in segments of 3, 4 and
 5 values, 512-thread workgroups with 4 and with 2 loads per lane, a grid
-of 512 workgroups (4096 wavefront slices).  The committed code passes
+of 512 workgroups (4096 wavefront slices).  The form of that time passes
 them all; each planted mistake (built with -DMUTATION=k) must fail.
 Mutation 4 is the reading of the removed change that admitted parts with
 as many starts as visible ring entries: it reads lane 64."""
