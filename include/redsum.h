@@ -30,7 +30,10 @@
  *     partials, barrier words, carry slots, error word), allocated on first
  *     use outside of stream capture, freed by red_shutdown().  Calls that
  *     overlap on the same stream are ordered by the stream; calls on
- *     different streams use different workspaces.
+ *     different streams use different workspaces.  A call recorded into a
+ *     graph uses the workspace of the stream it was recorded on, wherever the
+ *     graph is replayed: replays must not overlap other calls or replays
+ *     that use it.
  */
 #ifndef REDSUM_H
 #define REDSUM_H
