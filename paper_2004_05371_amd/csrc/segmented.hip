@@ -875,23 +875,30 @@ size_t seg_lds_bytes(int wg, int max_rows) {
 // The form of a launch: forced, or from the batch's mean segment length and,
 // for plans of at most 4 loads per thread, from the lengths of 64 segments
 // evenly spaced over the batch (the same decision in every workgroup; the
-// rules and their figures are in seg_rules.h).  The sample costs the forms
-// that it does not change 0.4 us (1 M values, equal lengths of 4096: 8.4 us
-// without it, 8.8 with).
+// rules and their figures are in seg_rules.h).  One wavefront per workgroup
+// takes the sample, 64 cache lines: taken by each of a CU's 16 wavefronts it
+// held up the loads behind it.
 template <int IPT>
-__device__ __forceinline__ int seg_form(const SegArgs& a) {
+__device__ __forceinline__ int seg_form(const SegArgs& a, int* shared) {
   if (a.form != kSegAuto) return a.form;
-  const v2l sample = *reinterpret_cast<const v2l*>(a.offsets + (((int64_t)__lane_id() * a.nseg) >> 6));
+  const bool sampler = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) == 0;
+  v2l sample = {0, 0};
+  if (IPT <= 4 && sampler)
+    sample = *reinterpret_cast<const v2l*>(a.offsets + (((int64_t)__lane_id() * a.nseg) >> 6));
   const int64_t E = offset_at(a.offsets, a.nseg);
   if constexpr (IPT <= 4) {
     if (short_batch(E, a.nseg, (int64_t)a.grid * a.wg)) return kSegWaveRuns;
     if (E < kRunsRaggedLen * a.nseg) {
-      const long long next = dpp_move<kWaveShl1, 0xF, 0xF>((long long)sample.x);
-      const SampledSegment l = sampled_segment(E, a.nseg, sample.x, sample.y, next);
-      auto lanes = [](bool p) { return (int)__popcll(__ballot(p)); };
-      const SegSample c{lanes(l.is_short), lanes(l.is_short && l.is_filled), lanes(l.is_filled), lanes(l.is_joined),
-                        lanes(l.is_long)};
-      if (ragged_batch(E, a.nseg, c)) return kSegWaveRuns;
+      if (sampler) {
+        const long long next = dpp_move<kWaveShl1, 0xF, 0xF>((long long)sample.x);
+        const SampledSegment l = sampled_segment(E, a.nseg, sample.x, sample.y, next);
+        auto lanes = [](bool p) { return (int)__popcll(__ballot(p)); };
+        const SegSample c{lanes(l.is_short), lanes(l.is_short && l.is_filled), lanes(l.is_filled), lanes(l.is_joined),
+                          lanes(l.is_long)};
+        if (__lane_id() == 0) *shared = ragged_batch(E, a.nseg, c) ? kSegWaveRuns : long_form(E, a.nseg);
+      }
+      __syncthreads();
+      return __builtin_amdgcn_readfirstlane(*shared);
     }
   }
   return long_form(E, a.nseg);
@@ -902,7 +909,8 @@ __global__ __launch_bounds__(kSegMaxWG) void k_segmented(SegArgs a) {
   extern __shared__ __align__(16) unsigned char seg_lds[];
   constexpr int MAX_ROWS = runs_max_rows(IPT, WIDE);
   SegLds<MAX_ROWS>& lds = *reinterpret_cast<SegLds<MAX_ROWS>*>(seg_lds);
-  const int form = seg_form<IPT>(a);
+  __shared__ int shared_form;
+  const int form = seg_form<IPT>(a, &shared_form);
   if (form == kSegWorkgroup) {
     seg_workgroup_slices<IPT, NT, FIX>(a, lds.wg);
   } else if (form == kSegWaveRuns) {
