@@ -138,7 +138,7 @@ struct Entry {
 
 int64_t first_at_or_after(Machine& b, int64_t pos) {
   int64_t L = 0, R = b.nseg;
-  while (R - L > kWave) {
+  while (R - L > 2 * kWave) {
     const int64_t d = R - L;
     int c = 0;
     for (int l = 0; l < kWave; ++l) {
@@ -151,7 +151,10 @@ int64_t first_at_or_after(Machine& b, int64_t pos) {
     if (c > 0) L = L + (((int64_t)c * d) >> 6) + 1;
   }
   int c = 0;
-  for (int l = 0; l < kWave; ++l) c += L + l < R && b.offset(L + l) < pos;
+  for (int64_t i = L; i < R && i < L + 2 * kWave; i += 2) {
+    const int64_t x = b.offset(i), y = b.offset(i + 1);
+    c += (x < pos) + (i + 1 < R && y < pos);
+  }
   return L + c;
 }
 
