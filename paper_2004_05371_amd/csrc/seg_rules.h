@@ -114,11 +114,16 @@ RED_HD bool ragged_batch(int64_t E, int64_t nseg, const SegSample& c) {
 // values in 15 log-uniform segments: 10.7 us against 18.9).
 constexpr int64_t kRunsMinChunk = 512;
 constexpr int64_t kRunsLongChunk = 4096;
+// The least where the values start `shift` > 0 elements past a 16-byte
+// boundary: 512 of them lie in one vector more than a tile of 2 rows holds, and
+// that vector costs a tile (random cuts of mean 2000, 270,000 values 7.2 us per
+// call against 8.0, 1.7 M 9.9 against 10.4).
+constexpr int64_t kRunsMinChunkShifted = 448;
 
 // Values of a slice of the reduce-by-key form over W wavefronts.
-RED_HD int64_t runs_slice(int64_t E, int64_t nseg, int64_t W) {
+RED_HD int64_t runs_slice(int64_t E, int64_t nseg, int64_t W, int shift) {
   const int64_t mean = (int64_t)((float)E / (float)nseg);
-  return std::max<int64_t>({kRunsMinChunk, (((E + W - 1) / W) + 63) & ~(int64_t)63,
+  return std::max<int64_t>({shift ? kRunsMinChunkShifted : kRunsMinChunk, (((E + W - 1) / W) + 63) & ~(int64_t)63,
                             std::min<int64_t>(mean / 16, kRunsLongChunk) & ~(int64_t)63});
 }
 

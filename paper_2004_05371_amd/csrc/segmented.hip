@@ -677,7 +677,7 @@ __device__ __forceinline__ void seg_wave_runs(const SegArgs& a, RunLds<MAX_ROWS>
   const int64_t w = (int64_t)blockIdx.x * nwaves + wv;
   const int64_t W = (int64_t)a.grid * nwaves;
   const int64_t E = offset_at(a.offsets, a.nseg);
-  const int64_t chunk = runs_slice(E, a.nseg, W);
+  const int64_t chunk = runs_slice(E, a.nseg, W, (int)((reinterpret_cast<uintptr_t>(a.x) & 15) >> 2));
   const int64_t lo = std::min(w * chunk, E);
   const int64_t hi = std::min(lo + chunk, E);
   const bool end_slice = E > 0 ? (lo < E && hi == E) : (w == 0);

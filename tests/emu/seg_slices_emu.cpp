@@ -79,6 +79,7 @@ struct Machine {
   std::vector<int64_t> own;  // barrier: cut segment that slice w owns
   long long halves = 0, scanned = 0, plain = 0, late_chunks = 0, cut = 0;
   int rows_used = 0;
+  int64_t max_tiles = 0;
 
   int64_t offset(int64_t i) {
     if (i < 0 || i > nseg) fail("offsets read out of bounds", i, nseg);
@@ -166,6 +167,7 @@ void Machine::wave(int64_t w, int64_t chunk, int ROWS) {
   const int64_t vlo = (lo + shift) >> 2, vhi = (hi + shift + 3) >> 2;
   const int64_t T = (int64_t)kWave * ROWS;
   const int64_t ntiles = lo < hi ? (vhi - vlo + T - 1) / T : 0;
+  max_tiles = std::max(max_tiles, ntiles);
 
   const int tile_size = run_tile_vectors(ROWS), max_sums = 2 * tile_size;  // 16-byte vectors, 8-byte sums
   if (tile_size > run_tile_vectors(max_rows)) fail("rows beyond the launch's buffer", ROWS, max_rows);
@@ -397,7 +399,7 @@ void Machine::run_launch() {
   out.assign(nseg, 0);
   writes.assign(nseg, 0);
   own.assign(W, -1);
-  const int64_t chunk = MUTATION == 9 ? std::max<int64_t>(kRunsMinChunk, E / nseg / 16 / 64 * 64) : runs_slice(E, nseg, W);
+  const int64_t chunk = MUTATION == 9 ? std::max<int64_t>(kRunsMinChunk, E / nseg / 16 / 64 * 64) : runs_slice(E, nseg, W, shift);
   rows_used = runs_rows(max_rows, chunk);
   // The wavefronts in an order of their own per launch.
   std::vector<int64_t> order(W);
@@ -470,8 +472,8 @@ int main(int argc, char** argv) {
   // Twice: the second launch finds what the first left in the slots.
   m.run_launch();
   m.run_launch();
-  printf("{\"ok\": true, \"segments\": %lld, \"rows\": %d, \"halves\": %lld, \"scanned\": %lld, \"plain\": %lld, "
+  printf("{\"ok\": true, \"segments\": %lld, \"rows\": %d, \"max_tiles\": %lld, \"halves\": %lld, \"scanned\": %lld, \"plain\": %lld, "
          "\"late_chunks\": %lld, \"cut\": %lld}\n",
-         (long long)m.nseg, m.rows_used, m.halves, m.scanned, m.plain, m.late_chunks, m.cut);
+         (long long)m.nseg, m.rows_used, (long long)m.max_tiles, m.halves, m.scanned, m.plain, m.late_chunks, m.cut);
   return 0;
 }

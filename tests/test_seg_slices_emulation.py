@@ -65,6 +65,13 @@ def test_launches(emu, case, fix):
     assert rec["rows"] == rows, rec
 
 
+@pytest.mark.parametrize("shift", range(4))
+def test_the_shortest_slices_are_one_tile(emu, shift):
+    """Also where the values are not aligned to 16 bytes."""
+    rec = run(emu, (1_000_003, 300, 1, 1024, 256, 4, 1, 0, shift, 17))
+    assert rec["ok"] and rec["rows"] == 2 and rec["max_tiles"] == 1, rec
+
+
 def test_every_branch_is_taken(emu):
     recs = [run(emu, c[:7] + (0,) + c[7:]) for c, _ in CASES]
     for rows in (2, 4, 8):
