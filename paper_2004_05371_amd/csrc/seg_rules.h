@@ -127,7 +127,7 @@ RED_HD int64_t runs_slice(int64_t E, int64_t nseg, int64_t W, int shift) {
                             std::min<int64_t>(mean / 16, kRunsLongChunk) & ~(int64_t)63});
 }
 
-// Rows of the largest tile.  The wide kernels keep 16 wavefronts per CU (125
+// Rows of the largest tile.  The wide kernels keep 16 wavefronts per CU (123
 // VGPRs with 8 rows), the others 20 and more; the host takes a wide one for a
 // grid that is then wholly resident.
 constexpr int runs_max_rows(int ipt, bool wide) { return ipt == 4 ? (wide ? 8 : 4) : ipt == 2 && wide ? 4 : 2; }
