@@ -382,9 +382,9 @@ __device__ __forceinline__ void seg_wave_slices(const SegArgs& a) {
 //
 // What bounds it is latency that four wavefronts per SIMD do not hide: the
 // steps of a tile depend on one another through LDS and memory.  By the
-// counters a wavefront waits for one of these 48 % of its time (32 M values in
-// segments of 16 on average) or 42 % (67 M in segments of 512), for its turn to
-// issue 26 and 31 %; the VALU is busy about a quarter of the time, LDS 23 and
+// counters a wavefront waits for one of these 47 % of its time (32 M values in
+// segments of 16 on average) or 41 % (67 M in segments of 512), for its turn to
+// issue 27 and 32 %; the VALU is busy about a quarter of the time, LDS 23 and
 // 29 %, 9 and 0.4 % of that with bank conflicts.  So the runs are as long as
 // four wavefronts have registers for, to spread a tile's fixed steps, about 250
 // operations, over more values (about 10 operations per row of 64; smaller

@@ -206,7 +206,7 @@ __global__ __launch_bounds__(1024) void k_jacobi_persistent(StencilArgs a) {
 // at 2.6 to 3.2 cycles each with two or more wavefronts per SIMD, 4.6 to 4.8
 // with one (by the counters: 4 M values, 200 steps, four wavefronts: 31,070
 // VALU instructions per SIMD in 81,000 cycles, waits for memory 14 % of the
-// wavefronts' time; 64 K values: 1368 per wavefront in 6540 cycles).
+// wavefronts' time; 64 K values: 1368 per wavefront in 6500 cycles).
 // ---------------------------------------------------------------------------
 
 // One step on the window.  The neighbour sums run one value ahead of the
